@@ -44,10 +44,10 @@ int launch_conv_signal_rows(const ConvArgs& a, float* sc, int64_t nbp, hipStream
 // segments of P = F - T + 1 output rows, T = (N + L - 2) / L + 1 taps per phase.
 struct ConvFftGeom {
     int64_t nout, rows, T;
-    int F, logF;
+    int F;
     int64_t P, nseg, nbp;
     bool ok;                 // T fits the largest transform with P >= 1
-    int64_t sc_bytes, tw_bytes, hf_bytes, sf_bytes, yf_bytes, total;
+    int64_t sc_bytes, kd_bytes, hf_bytes, sf_bytes, yf_bytes, total;
 };
 ConvFftGeom conv_fft_geom(int64_t W, int64_t N, int L, int r);
 int launch_conv_fft(const ConvArgs& a, hipStream_t s);
