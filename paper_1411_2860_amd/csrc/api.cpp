@@ -663,7 +663,7 @@ int plan_batch(int count, const pj_gemm_desc* p, int L, int r, int prec, int til
     }
     if ((prec == PJ_FP8 || prec == PJ_FP8X2) && r > 8) return PJ_ERR_UNSUPPORTED;
     bp.cfg = tile_cfg;
-    if (bp.cfg < 0) bp.cfg = 0;
+    if (bp.cfg < 0) bp.cfg = gemm_grouped_default_config(prec);
     int tm = 0, tn = 0, sm = 0, sn = 0;
     gemm_config_tile(prec, bp.cfg, &tm, &tn);
     gemm_config_small_tile(prec, bp.cfg, &sm, &sn);
@@ -776,10 +776,13 @@ static int run_batched(pj_basis b, int r, int count, const pj_gemm_desc* problem
         for (int64_t y = 0; y < ntn; ++y)
             for (int64_t x = 0; x < ntm; ++x) items.push_back(GroupedItem{i, (int32_t)x, (int32_t)y, body});
     }
-    // longest contractions first (stable: problem order, then tile order)
+    // the configuration's tiles before the small ones, longest contractions
+    // first (stable: problem order, then tile order)
     std::stable_sort(items.begin(), items.end(), [&](const GroupedItem& u, const GroupedItem& v) {
-        return gp[u.prob].nkb > gp[v.prob].nkb;
+        return u.body != v.body ? u.body < v.body : gp[u.prob].nkb > gp[v.prob].nkb;
     });
+    int64_t nbig = 0;
+    while (nbig < (int64_t)items.size() && items[nbig].body == 0) ++nbig;
     for (const PackArgs& x : pa)
         if (x.geom.nrb * (x.geom.Gp / ly.KB) > 0x3fffffff) return PJ_ERR_UNSUPPORTED;
     rc = launch_pack_grouped(prec, pa.data(), 2 * count, w, st);
@@ -790,7 +793,7 @@ static int run_batched(pj_basis b, int r, int count, const pj_gemm_desc* problem
                        st) != hipSuccess)
         return PJ_ERR_HIP;
     rc = launch_gemm_grouped(prec, (const GroupedProblem*)(w + bp.probs_off), (const GroupedItem*)(w + bp.items_off),
-                             bp.nitems, device_cus(), bp.cfg, st);
+                             bp.nitems, nbig, device_cus(), bp.cfg, st);
     return rc == 0 ? PJ_OK : (rc == -2 ? PJ_ERR_UNSUPPORTED : PJ_ERR_HIP);
 }
 

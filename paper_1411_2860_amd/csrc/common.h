@@ -106,6 +106,18 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
+// A pointer into device memory that was itself read from memory (a job or
+// problem table).  The compiler cannot see that it is not an LDS address and
+// falls back to flat accesses, which count as LDS traffic too, so that every
+// wait for one of them drains all loads in flight; through the global address
+// space they stay ordinary global loads and stores.
+template <typename T>
+__device__ __forceinline__ T* global_ptr(T* p)
+{
+    using G = __attribute__((address_space(1))) T;
+    return (T*)(G*)(uintptr_t)p;
+}
+
 // Launch helpers implemented in the .hip files (host side).
 struct PackArgs {
     const void* X;     // float or double source
@@ -173,10 +185,11 @@ struct GroupedItem {
     int32_t tm, tn;      // tile of the item's body
     int32_t body;        // 0: the launch's tile configuration; 1: its small tile
 };                       // (one MFMA block per wave, same waves)
-// Persistent launch over `nitems` items: as many workgroups as `cus` compute
-// units hold at once (at most one per item).
+// Persistent launch over `nitems` items, the first `nbig` of them with body 0 and
+// the others with body 1: as many workgroups as `cus` compute units hold at
+// once (at most one per item).
 int launch_gemm_grouped(int prec, const GroupedProblem* probs, const GroupedItem* items, int64_t nitems,
-                        int64_t cus, int cfg, hipStream_t s);
+                        int64_t nbig, int64_t cus, int cfg, hipStream_t s);
 
 // cfg < 0 picks the default tile configuration for the shape.
 int launch_gemm(int prec, const GemmArgs& a, int cfg, hipStream_t s);
@@ -185,6 +198,7 @@ int gemm_config_tile(int prec, int cfg, int* tile_m, int* tile_n);
 // The small tile grouped launches of configuration cfg can also run.
 int gemm_config_small_tile(int prec, int cfg, int* tile_m, int* tile_n);
 int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb);
+int gemm_grouped_default_config(int prec);
 int gemm_split_count(int prec, int64_t P, int64_t Q, int64_t nkb, int cfg);
 
 }  // namespace pj

@@ -846,27 +846,209 @@ __global__ __launch_bounds__(256) void gemm_split_sum_kernel(const OT* __restric
     R[p * ldr + q] = v;
 }
 
-// Persistent grouped launch: workgroup b processes items b, b + grid, ... of
-// a list of (problem, tile) items sorted by decreasing contraction length, so
-// the longest tiles start first and the tail is made of short ones.  Each
-// item names its body: the configuration's tile, or the small tile of one
-// MFMA block per wave on the same waves (for problems whose sides the large
-// tile would mostly pad).
-template <int KIND, int PREC, int WM, int WN, int WAVES_M, int WAVES_N, int OCC>
-__global__ PJ_GEMM_BOUNDS void gemm_grouped_kernel(
-    const GroupedProblem* __restrict__ probs, const GroupedItem* __restrict__ items, int64_t nitems)
+// Persistent grouped launch over a list of (problem, tile) items sorted by
+// decreasing contraction length, so the longest tiles start first and the tail
+// is made of short ones.  The first nbig items run in the configuration's
+// tile, the others in the small tile of one MFMA block per wave on the same
+// waves (for problems whose sides the large tile would mostly pad).  Round k
+// deals items [k grid, (k + 1) grid), neighbouring items (tiles of one problem
+// that share operand panels) to one XCD, as in the single launch.
+__device__ __forceinline__ int64_t grouped_item(int64_t k, int64_t lo, int64_t hi)
 {
-    for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
+    const int64_t base = lo + k * gridDim.x;
+    const int64_t n = hi - base < gridDim.x ? hi - base : gridDim.x;
+    return blockIdx.x < n ? base + xcd_remap(blockIdx.x, n) : -1;
+}
+
+// The items of one workgroup as ONE stream of steps through the copy ring of
+// gemm_tile_dma_ra: the copies run NS steps ahead of the matrix instructions
+// across item boundaries, so an item costs neither a ring fill nor the chain
+// of descriptor loads in front of it, and its output stores overlap with the
+// copies of the next.  An item of 256 x 128 outputs in a launch of its own spends
+// about 8 us outside its matrix work (2 us to the first product, 6 us of stores
+// that the whole chip issues together), as much as 1024 indices of BF16x3.
+// Against one item after another: 24 problems, r = 4, 891 -> 865 us (BF16x3) and
+// 701 -> 677 us (BF16); the matrix work runs at 1.2 PFLOP/s, the stores (550 MB)
+// cost the remaining 75 .. 95 us.  An item's steps are rounded up to an even number (register sets alternate with
+// the step parity); k-blocks below 0 are zeroed in LDS once their copy, which
+// reads k-block 0, has landed (zmask: one bit per copy of a stage).
+template <int PREC, int WM, int WN, int WAVES_M, int WAVES_N, int NS, int KS, bool ILV>
+__device__ __forceinline__ void gemm_stream(const GroupedProblem* __restrict__ probs,
+                                            const GroupedItem* __restrict__ items, int64_t nbig)
+{
+    using T = MT<PREC>;
+    using frag = typename T::frag;
+    using acc_t = typename T::acc;
+    constexpr int PL = T::PLANES;
+    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int BMB = WM * WAVES_M, BNB = WN * WAVES_N;
+    constexpr int NTILE = (BMB + BNB) * PL;
+    constexpr int NSLOT = NTILE * KS;
+    constexpr int PER_W = NSLOT / NW;
+    constexpr int NCH = NSLOT * 64;
+    static_assert(sizeof(frag) == 16, "LDS path is for 16-byte lane formats");
+    static_assert(NSLOT % NW == 0, "every wave issues the same number of copies");
+    static_assert((NS & (NS - 1)) == 0 && (NS - 1) * PER_W < 64, "ring slots, in-flight copy count");
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    f32x4* lds = reinterpret_cast<f32x4*>(smem_raw);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+    int64_t it = grouped_item(0, 0, nbig);
+    if (it < 0) return;
+
+    // ---- producer: copies of step pst of the pk-th item -------------------
+    const char* srcw[PER_W];
+    int64_t pk = 0;
+    int pnk = 0, pst = 0, pnst = 0;
+    auto open = [&](int64_t idx) {
+        const GroupedItem w = items[idx];
+        const GroupedProblem& p = probs[w.prob];
+        pnk = (int)p.nkb;
+        pst = 0;
+        pnst = (pnk + 2 * KS - 1) / (2 * KS) * 2;
+#pragma unroll
+        for (int i = 0; i < PER_W; ++i) {
+            const int ti = (wave + i * NW) % NTILE;
+            const int blk = ti / PL, pl = ti % PL;
+            if (blk < BMB) {
+                const int64_t rb = (int64_t)w.tm * BMB + blk;
+                srcw[i] = global_ptr((const char*)p.X) + pl * p.x_plane + (rb < p.x_nrb ? rb : 0) * p.x_nkb * 1024;
+            } else {
+                const int64_t cb = (int64_t)w.tn * BNB + blk - BMB;
+                srcw[i] = global_ptr((const char*)p.Y) + pl * p.y_plane + (cb < p.y_nrb ? cb : 0) * p.y_nkb * 1024;
+            }
+        }
+    };
+    unsigned zring[NS];                       // zmask of the stages in flight, oldest first
+    auto copy = [&](int slot) -> unsigned {
+        unsigned z = 0;
+#pragma unroll
+        for (int i = 0; i < PER_W; ++i) {
+            const int kb = pnk - 1 - pst * KS - (wave + i * NW) / NTILE;
+            z |= (unsigned)(kb < 0) << i;
+            const char* src = srcw[i] + (int64_t)(kb < 0 ? 0 : kb) * 1024 + lane * 16;
+            __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(src),
+                                             reinterpret_cast<void*>(lds + slot * NCH + (wave + i * NW) * 64), 16, 0,
+                                             0);
+        }
+        if (++pst == pnst) {
+            const int64_t next = grouped_item(++pk, 0, nbig);
+            if (next >= 0) open(next);
+            else pnst = -1;                   // no item left: the copies go on (counted waits) and are never read
+        }
+        return z;
+    };
+    auto fix = [&](int slot, unsigned z) {
+#pragma unroll
+        for (int i = 0; i < PER_W; ++i)
+            if ((z >> i) & 1) lds[slot * NCH + (wave + i * NW) * 64 + lane] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+
+    // ---- consumer ---------------------------------------------------------
+    acc_t acc[WM][WN];
+    frag fa[2][KS][WM][PL], fb[2][KS][WN][PL];
+    auto read = [&](int slot, int set) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const f32x4* base = lds + slot * NCH + k * NTILE * 64;
+#pragma unroll
+            for (int a = 0; a < WM; ++a)
+#pragma unroll
+                for (int pl = 0; pl < PL; ++pl)
+                    fa[set][k][a][pl] = *reinterpret_cast<const frag*>(&base[((wm * WM + a) * PL + pl) * 64 + lane]);
+#pragma unroll
+            for (int b = 0; b < WN; ++b)
+#pragma unroll
+                for (int pl = 0; pl < PL; ++pl)
+                    fb[set][k][b][pl] =
+                        *reinterpret_cast<const frag*>(&base[((BMB + wn * WN + b) * PL + pl) * 64 + lane]);
+        }
+    };
+    constexpr int AHEAD = (NS - 2) * PER_W;
+    int slot = 0;                             // ring slot of the step being contracted
+    auto step = [&](int set) {
+        const int nslot = (slot + 1) & (NS - 1);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");      // own copies of the next stage
+        if (zring[1]) fix(nslot, zring[1]);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        const unsigned z = copy(slot);
+#pragma unroll
+        for (int i = 0; i + 1 < NS; ++i) zring[i] = zring[i + 1];
+        zring[NS - 1] = z;
+        read(nslot, set ^ 1);
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+#pragma unroll
+            for (int a = 0; a < WM; ++a)
+#pragma unroll
+                for (int b = 0; b < WN; ++b) T::mma(acc[a][b], fa[set][k][a], fb[set][k][b]);
+        if constexpr (ILV) {
+            constexpr int NR = KS * (WM + WN) * PL;
+            constexpr int NM = KS * WM * WN * T::NMMA;
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, NM / NR, 0);
+            }
+            if constexpr (NM % NR != 0) __builtin_amdgcn_sched_group_barrier(0x008, NM % NR, 0);
+        }
+        slot = nslot;
+    };
+
+    open(it);
+#pragma unroll
+    for (int d = 0; d < NS; ++d) zring[d] = copy(d);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * PER_W) : "memory");
+    if (zring[0]) fix(0, zring[0]);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    read(0, 0);
+    for (int64_t k = 0; it >= 0; it = grouped_item(++k, 0, nbig)) {
         const GroupedItem w = items[it];
         const GroupedProblem& p = probs[w.prob];
-        if (w.body == 0)
+        const int nk = (int)p.nkb;
+        const int nst = (nk + 2 * KS - 1) / (2 * KS) * 2;
+#pragma unroll
+        for (int a = 0; a < WM; ++a)
+#pragma unroll
+            for (int b = 0; b < WN; ++b)
+#pragma unroll
+                for (int j = 0; j < T::NACC; ++j) acc[a][b][j] = 0;
+        for (int st = 0; st < nst; st += 2) {
+            step(0);
+            step(1);
+        }
+        store_tile<PREC, WM, WN>(acc, lane, ((int64_t)w.tm * WAVES_M + wm) * WM, ((int64_t)w.tn * WAVES_N + wn) * WN,
+                                 p.P, p.Q, global_ptr((typename T::out_t*)p.R), p.ldr, p.beta);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy outlives the workgroup's LDS
+}
+
+template <int KIND, int PREC, int WM, int WN, int WAVES_M, int WAVES_N, int OCC>
+__global__ PJ_GEMM_BOUNDS void gemm_grouped_kernel(
+    const GroupedProblem* __restrict__ probs, const GroupedItem* __restrict__ items, int64_t nitems, int64_t nbig)
+{
+    if constexpr ((KIND == 4 || KIND == 5) && sizeof(typename MT<PREC>::frag) == 16) {
+        gemm_stream<PREC, WM, WN, WAVES_M, WAVES_N, 4, gemm_lds_ks<PREC, WM, WN, WAVES_M, WAVES_N>(), KIND == 5>(
+            probs, items, nbig);
+    } else {
+        int64_t it;
+        for (int64_t k = 0; (it = grouped_item(k, 0, nbig)) >= 0; ++k) {
+            const GroupedItem w = items[it];
+            const GroupedProblem& p = probs[w.prob];
             gemm_any<KIND, PREC, WM, WN, WAVES_M, WAVES_N>(
-                (const char*)p.X, p.x_nrb, p.x_nkb, p.x_plane, p.x_pb, (const char*)p.Y, p.y_nrb, p.y_nkb,
-                p.y_plane, p.y_pb, p.nkb, 0, p.P, p.Q, (typename MT<PREC>::out_t*)p.R, p.ldr, p.beta, w.tm, w.tn);
-        else
-            gemm_any<0, PREC, 1, 1, WAVES_M, WAVES_N>(
-                (const char*)p.X, p.x_nrb, p.x_nkb, p.x_plane, p.x_pb, (const char*)p.Y, p.y_nrb, p.y_nkb,
-                p.y_plane, p.y_pb, p.nkb, 0, p.P, p.Q, (typename MT<PREC>::out_t*)p.R, p.ldr, p.beta, w.tm, w.tn);
+                global_ptr((const char*)p.X), p.x_nrb, p.x_nkb, p.x_plane, p.x_pb, global_ptr((const char*)p.Y), p.y_nrb, p.y_nkb,
+                p.y_plane, p.y_pb, p.nkb, 0, p.P, p.Q, global_ptr((typename MT<PREC>::out_t*)p.R), p.ldr, p.beta, w.tm, w.tn);
+        }
+    }
+    // the small tiles, dealt from the workgroup that follows the last large one
+    const int64_t first = nbig % gridDim.x;
+    for (int64_t it = nbig + (blockIdx.x + gridDim.x - first) % gridDim.x; it < nitems; it += gridDim.x) {
+        const GroupedItem w = items[it];
+        const GroupedProblem& p = probs[w.prob];
+        gemm_any<0, PREC, 1, 1, WAVES_M, WAVES_N>(
+            global_ptr((const char*)p.X), p.x_nrb, p.x_nkb, p.x_plane, p.x_pb, global_ptr((const char*)p.Y), p.y_nrb, p.y_nkb,
+            p.y_plane, p.y_pb, p.nkb, 0, p.P, p.Q, global_ptr((typename MT<PREC>::out_t*)p.R), p.ldr, p.beta, w.tm, w.tn);
     }
 }
 
@@ -940,8 +1122,8 @@ constexpr TileCfg kTileCfgs[] = {
 constexpr int kNumTileCfgs = (int)(sizeof(kTileCfgs) / sizeof(kTileCfgs[0]));
 
 template <int KIND, int PREC, int WM, int WN, int WAVES_M, int WAVES_N, int OCC>
-int launch_grouped_t(const GroupedProblem* probs, const GroupedItem* items, int64_t nitems, int64_t cus,
-                     hipStream_t s)
+int launch_grouped_t(const GroupedProblem* probs, const GroupedItem* items, int64_t nitems, int64_t nbig,
+                     int64_t cus, hipStream_t s)
 {
     constexpr size_t lds = gemm_lds_bytes<KIND, PREC, WM, WN, WAVES_M, WAVES_N>();
     const void* kern = (const void*)gemm_grouped_kernel<KIND, PREC, WM, WN, WAVES_M, WAVES_N, OCC>;
@@ -953,17 +1135,17 @@ int launch_grouped_t(const GroupedProblem* probs, const GroupedItem* items, int6
         per_cu = 1;
     const int64_t grid = std::min<int64_t>(nitems, (int64_t)per_cu * cus);
     hipLaunchKernelGGL((gemm_grouped_kernel<KIND, PREC, WM, WN, WAVES_M, WAVES_N, OCC>), dim3((unsigned)grid),
-                       dim3(64 * WAVES_M * WAVES_N), lds, s, probs, items, nitems);
+                       dim3(64 * WAVES_M * WAVES_N), lds, s, probs, items, nitems, nbig);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 template <int PREC>
-int launch_grouped_cfg(const GroupedProblem* probs, const GroupedItem* items, int64_t nitems, int64_t cus, int cfg,
-                       hipStream_t s)
+int launch_grouped_cfg(const GroupedProblem* probs, const GroupedItem* items, int64_t nitems, int64_t nbig,
+                       int64_t cus, int cfg, hipStream_t s)
 {
     switch (cfg) {
 #define PJ_CFG_CASE(i, k_, a_, b_, c_, d_, o_) \
-    case i: return launch_grouped_t<k_, PREC, a_, b_, c_, d_, o_>(probs, items, nitems, cus, s);
+    case i: return launch_grouped_t<k_, PREC, a_, b_, c_, d_, o_>(probs, items, nitems, nbig, cus, s);
         PJ_GEMM_CONFIGS(PJ_CFG_CASE)
 #undef PJ_CFG_CASE
     default: return -2;
@@ -986,17 +1168,17 @@ int launch_cfg(const GemmArgs& a, int cfg, hipStream_t s)
 int gemm_num_configs() { return kNumTileCfgs; }
 
 int launch_gemm_grouped(int prec, const GroupedProblem* probs, const GroupedItem* items, int64_t nitems,
-                        int64_t cus, int cfg, hipStream_t s)
+                        int64_t nbig, int64_t cus, int cfg, hipStream_t s)
 {
     switch (prec) {
-    case P_F64:    return launch_grouped_cfg<P_F64>(probs, items, nitems, cus, cfg, s);
-    case P_F32:    return launch_grouped_cfg<P_F32>(probs, items, nitems, cus, cfg, s);
-    case P_BF16:   return launch_grouped_cfg<P_BF16>(probs, items, nitems, cus, cfg, s);
-    case P_BF16X3: return launch_grouped_cfg<P_BF16X3>(probs, items, nitems, cus, cfg, s);
-    case P_F16:    return launch_grouped_cfg<P_F16>(probs, items, nitems, cus, cfg, s);
-    case P_F16X3:  return launch_grouped_cfg<P_F16X3>(probs, items, nitems, cus, cfg, s);
-    case P_FP8:    return launch_grouped_cfg<P_FP8>(probs, items, nitems, cus, cfg, s);
-    case P_FP8X2:  return launch_grouped_cfg<P_FP8X2>(probs, items, nitems, cus, cfg, s);
+    case P_F64:    return launch_grouped_cfg<P_F64>(probs, items, nitems, nbig, cus, cfg, s);
+    case P_F32:    return launch_grouped_cfg<P_F32>(probs, items, nitems, nbig, cus, cfg, s);
+    case P_BF16:   return launch_grouped_cfg<P_BF16>(probs, items, nitems, nbig, cus, cfg, s);
+    case P_BF16X3: return launch_grouped_cfg<P_BF16X3>(probs, items, nitems, nbig, cus, cfg, s);
+    case P_F16:    return launch_grouped_cfg<P_F16>(probs, items, nitems, nbig, cus, cfg, s);
+    case P_F16X3:  return launch_grouped_cfg<P_F16X3>(probs, items, nitems, nbig, cus, cfg, s);
+    case P_FP8:    return launch_grouped_cfg<P_FP8>(probs, items, nitems, nbig, cus, cfg, s);
+    case P_FP8X2:  return launch_grouped_cfg<P_FP8X2>(probs, items, nitems, nbig, cus, cfg, s);
     default:       return -2;
     }
 }
@@ -1041,6 +1223,23 @@ int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb)
         // those tiles are one round on the chip (with more rounds the shorter
         // prologue of the LDS-staged 128 x 256 tile wins below 64)
         return (nkb >= 64 || (nkb >= 16 && cdiv(P, 256) * cdiv(Q, 128) <= 256)) ? 16 : 9;
+    }
+}
+
+// Grouped launches.  16-bit formats: the copy ring, whose stream runs across
+// items, on 256 x 128 tiles (24 problems with sides 128 .. 4096, r = 4, whole
+// call: BF16x3 1042 -> 843 us and BF16 765 -> 648 us against the direct
+// 128 x 128 tile of before; 128 x 128 rings 855 and 670; r = 16 BF16x3
+// contraction 3.54 -> 1.66 ms; up to sides of 512 the choice does not matter,
+// up to 2048 it is 251 -> 230 us).  FP32: the same ring on 128 x 128 tiles, two workgroups
+// a CU (1785 -> 1522 us; 256 x 128 interleaved 1604).  FP64 and FP8 have no
+// ring: direct 128 x 128 blocks.
+int gemm_grouped_default_config(int prec)
+{
+    switch (prec) {
+    case P_BF16: case P_BF16X3: case P_F16: case P_F16X3: return 16;
+    case P_F32: return 17;
+    default: return 0;
     }
 }
 
