@@ -750,7 +750,12 @@ __attribute__((amdgpu_waves_per_eu(pack_waves_per_eu<TIn, PREC, RL, NCH, LAY, tr
         if (prefix[mid] <= b) lo = mid;
         else hi = mid - 1;
     }
-    pack_tile<TIn, PREC, RL, NCH, LAY>(jobs[lo], b - prefix[lo]);
+    PackJob<TIn> j = jobs[lo];
+    j.X = global_ptr(j.X);
+    j.coef = global_ptr(j.coef);
+    j.out = global_ptr(j.out);
+    j.keep = global_ptr(j.keep);
+    pack_tile<TIn, PREC, RL, NCH, LAY>(j, b - prefix[lo]);
 }
 
 template <typename TIn, int PREC>
@@ -912,9 +917,10 @@ int launch_p(const PackArgs* a, int n, hipStream_t s)
 // a time with vector FMAs, the coefficients broadcast from LDS; a thread
 // keeps the E consecutive groups of one lane vector and writes it, so the 32
 // threads of a row block write one contiguous half-tile.  Workgroup = 256
-// columns x one k-block of groups, for every projection.
+// columns x one lane vector of groups, for every projection (a whole k-block of
+// groups a workgroup leaves 2321 workgroups where 2048 fit at once: a second,
+// nearly empty round).
 constexpr int kColW = 256;
-constexpr int kColRL = 16;
 constexpr int kColMaxL = 256;   // the library's largest projection size
 
 template <typename TIn>
@@ -929,82 +935,120 @@ struct ColJob {
     TIn* keep; int64_t keep_ld;
 };
 
-template <typename TIn, int PREC>
+// RL projections at a time (1, 2, 4, 8 or 16: no more than r needs, so that
+// few projections leave the registers to loads in flight): the rows of
+// col_depth<RL>() - 1 further indices t, E groups each, are on their way while
+// one index is accumulated.  24 problems, r = 4 (547 MB read, 145 MB written):
+// 203 -> 176 us against 16 projections at a time in tiles of two lane vectors.
+template <int RL> constexpr int col_depth() { return RL <= 4 ? 4 : 2; }
+
+template <typename TIn, int PREC, int RL>
 __device__ __forceinline__ void colpack_tile(const ColJob<TIn>& J, int64_t tix)
 {
     constexpr Layout ly = layout_of(PREC);
     constexpr int KB = ly.KB, RB = ly.RB, E = ly.E;
+    constexpr int D = col_depth<RL>();
     static_assert(KB % E == 0 && E <= 8, "lane vectors of at most 8 values");
-    __shared__ TIn cs[kColMaxL * kColRL];   // coefficients of the pass: [t][l - l0]
-    const int64_t ct = tix % J.ncol, gt = tix / J.ncol;
+    __shared__ TIn cs[kColMaxL * RL];       // coefficients of the pass: [t][l - l0]
+    const int64_t ct = tix % J.ncol, gv = tix / J.ncol;      // column tile, lane vector of groups
     const int64_t p = ct * kColW + threadIdx.x;
-    const int64_t j0 = gt * KB;
+    const int64_t j0 = gv * E / KB * KB;
+    const int g0 = (int)(gv * E - j0);
     const int L = J.L, r = J.r;
     const bool live = p < J.P;
-    const int64_t pc = live ? p : J.P - 1;   // reads stay inside the source
-    for (int l0 = 0; l0 < r; l0 += kColRL) {
+    const TIn* __restrict__ base = J.X + ct * kColW;
+    // byte offset of the lane's column; reads stay inside the source
+    const unsigned col = (live ? threadIdx.x : (unsigned)(J.P - 1 - ct * kColW)) * (unsigned)sizeof(TIn);
+    for (int l0 = 0; l0 < r; l0 += RL) {
         __syncthreads();
-        for (int x = threadIdx.x; x < L * kColRL; x += kColW) {
-            const int t = x / kColRL, lq = x % kColRL;
+        for (int x = threadIdx.x; x < L * RL; x += kColW) {
+            const int t = x / RL, lq = x % RL;
             cs[x] = l0 + lq < r ? J.coef[(int64_t)t * L + l0 + lq] : (TIn)0;
         }
         __syncthreads();
-        for (int g0 = 0; g0 < KB; g0 += E) {
-            TIn acc[kColRL][E];
+        TIn acc[RL][E];
 #pragma unroll
-            for (int q = 0; q < kColRL; ++q)
+        for (int q = 0; q < RL; ++q)
 #pragma unroll
-                for (int e = 0; e < E; ++e) acc[q][e] = (TIn)0;
-            // rows past K read row K - 1 and count as zero; the loads of
-            // index t + 1 are issued before the products of index t
-            auto ld = [&](int t, TIn (&x)[E]) {
+            for (int e = 0; e < E; ++e) acc[q][e] = (TIn)0;
+        // Row addresses are wave-uniform, the column a 32-bit lane offset: a
+        // load is one scalar addition and no vector work.  The row address
+        // is opaque to the compiler, which otherwise forms per-lane addresses
+        // of the whole loop ahead of it (198 registers, two waves per SIMD).
+        const int64_t k0 = (j0 + g0) * L;
+        auto fma = [&](int t, const TIn (&x)[E]) {
+            const TIn* c = cs + t * RL;
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const int64_t k = (j0 + g0 + e) * L + t;
-                    x[e] = J.X[(k < J.K ? k : J.K - 1) * J.ld + pc];
+            for (int e = 0; e < E; ++e)
+#pragma unroll
+                for (int q = 0; q < RL; ++q) acc[q][e] += c[q] * x[e];
+        };
+        // whole lane vectors, and the loads ahead of them, inside the source;
+        // vectors of padding groups (past K) stay zero
+        if (k0 >= J.K) {
+        } else if (k0 + (int64_t)E * L + D <= J.K) {
+            const char* row = reinterpret_cast<const char*>(base + k0 * J.ld);
+            const int64_t step = J.ld * (int64_t)sizeof(TIn), estep = step * L;
+            auto ld = [&](TIn (&x)[E]) {
+                const char* q = row;
+#pragma unroll
+                for (int e = 0; e < E; ++e, q += estep) {
+                    uintptr_t u = (uintptr_t)q;
+                    asm volatile("" : "+s"(u));
+                    using GB = const __attribute__((address_space(1))) char;
+                    using GT = const __attribute__((address_space(1))) TIn;
+                    x[e] = *(GT*)((GB*)u + col);
                 }
+                row += step;
             };
-            auto fma = [&](int t, const TIn (&x)[E]) {
-                const TIn* c = cs + t * kColRL;
+            TIn x[D][E];
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const TIn xe = (j0 + g0 + e) * L + t < J.K ? x[e] : (TIn)0;
+            for (int d = 0; d + 1 < D; ++d) ld(x[d]);
+            int t = 0;
+            for (; t + D <= L; t += D) {
 #pragma unroll
-                    for (int q = 0; q < kColRL; ++q) acc[q][e] += c[q] * xe;
-                }
-            };
-            TIn xa[E], xb[E];
-            ld(0, xa);
-            for (int t = 0; t < L; t += 2) {
-                if (t + 1 < L) ld(t + 1, xb);
-                fma(t, xa);
-                if (t + 1 < L) {
-                    if (t + 2 < L) ld(t + 2, xa);
-                    fma(t + 1, xb);
+                for (int d = 0; d < D; ++d) {
+                    ld(x[(d + D - 1) % D]);
+                    fma(t + d, x[d]);
                 }
             }
-            if (live) {
-                const int64_t rb = p / RB;
-                const int rib = (int)(p % RB), g = g0 / E;
 #pragma unroll
-                for (int q = 0; q < kColRL; ++q) {
-                    const int l = l0 + q;
-                    if (l >= r) break;
-                    const int64_t kb = ((int64_t)l * J.Gp + j0) / KB;
-                    const int64_t off = ((rb * J.nkb + kb) * 64 + g * RB + rib) * (int64_t)ly.LB;
-                    store_lane<PREC, E, TIn>(J.out, off, J.plane_stride, 0, acc[q]);
-                    if (J.keep) {
-                        TIn* dst = J.keep + p * J.keep_ld + (int64_t)l * J.Gp + j0 + g0;
+            for (int d = 0; d + 1 < D; ++d)
+                if (t + d < L) fma(t + d, x[d]);
+        } else {
+            for (int t = 0; t < L; ++t) {
+                TIn x[E];
 #pragma unroll
-                        for (int e = 0; e < E; ++e) dst[e] = acc[q][e];
-                    }
+                for (int e = 0; e < E; ++e) {
+                    const int64_t k = k0 + (int64_t)e * L + t;
+                    const char* q = reinterpret_cast<const char*>(base + (k < J.K ? k : J.K - 1) * J.ld);
+                    const TIn v = *reinterpret_cast<const TIn*>(q + col);
+                    x[e] = k < J.K ? v : (TIn)0;
+                }
+                fma(t, x);
+            }
+        }
+        if (live) {
+            const int64_t rb = p / RB;
+            const int rib = (int)(p % RB), g = g0 / E;
+#pragma unroll
+            for (int q = 0; q < RL; ++q) {
+                const int l = l0 + q;
+                if (l >= r) break;
+                const int64_t kb = ((int64_t)l * J.Gp + j0) / KB;
+                const int64_t off = ((rb * J.nkb + kb) * 64 + g * RB + rib) * (int64_t)ly.LB;
+                store_lane<PREC, E, TIn>(J.out, off, J.plane_stride, 0, acc[q]);
+                if (J.keep) {
+                    TIn* dst = J.keep + p * J.keep_ld + (int64_t)l * J.Gp + j0 + g0;
+#pragma unroll
+                    for (int e = 0; e < E; ++e) dst[e] = acc[q][e];
                 }
             }
         }
     }
 }
 
-template <typename TIn, int PREC>
+template <typename TIn, int PREC, int RL>
 __global__ __launch_bounds__(kColW) void colpack_grouped_kernel(const ColJob<TIn>* __restrict__ jobs,
                                                                const int64_t* __restrict__ prefix, int njobs)
 {
@@ -1015,7 +1059,12 @@ __global__ __launch_bounds__(kColW) void colpack_grouped_kernel(const ColJob<TIn
         if (prefix[mid] <= b) lo = mid;
         else hi = mid - 1;
     }
-    colpack_tile<TIn, PREC>(jobs[lo], b - prefix[lo]);
+    ColJob<TIn> j = jobs[lo];
+    j.X = global_ptr(j.X);
+    j.coef = global_ptr(j.coef);
+    j.out = global_ptr(j.out);
+    j.keep = global_ptr(j.keep);
+    colpack_tile<TIn, PREC, RL>(j, b - prefix[lo]);
 }
 
 template <typename TIn, int PREC>
@@ -1053,7 +1102,7 @@ int launch_colpack_grouped(const PackArgs* a, int n, char* jobs_at, char* prefix
         std::vector<int64_t> prefix(n + 1, 0);
         for (int i = 0; i < n; ++i) {
             jobs[i] = make_coljob<TIn, PREC>(a[i]);
-            prefix[i + 1] = prefix[i] + jobs[i].ncol * (a[i].geom.Gp / layout_of(PREC).KB);
+            prefix[i + 1] = prefix[i] + jobs[i].ncol * (a[i].geom.Gp / layout_of(PREC).E);
         }
         if (prefix[n] == 0) return 0;
         if (prefix[n] > 0x7fffffff) return -2;
@@ -1061,8 +1110,17 @@ int launch_colpack_grouped(const PackArgs* a, int n, char* jobs_at, char* prefix
             hipMemcpyAsync(prefix_at, prefix.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, s) !=
                 hipSuccess)
             return -1;
-        hipLaunchKernelGGL((colpack_grouped_kernel<TIn, PREC>), dim3((unsigned)prefix[n]), dim3(kColW), 0, s,
-                           (const ColJob<TIn>*)jobs_at, (const int64_t*)prefix_at, n);
+        int r = 1;
+        for (int i = 0; i < n; ++i) r = a[i].r > r ? a[i].r : r;
+#define PJ_COL(RL_)                                                                                            \
+    hipLaunchKernelGGL((colpack_grouped_kernel<TIn, PREC, RL_>), dim3((unsigned)prefix[n]), dim3(kColW), 0, s, \
+                       (const ColJob<TIn>*)jobs_at, (const int64_t*)prefix_at, n)
+        if (r == 1) PJ_COL(1);
+        else if (r == 2) PJ_COL(2);
+        else if (r <= 4) PJ_COL(4);
+        else if (r <= 8) PJ_COL(8);
+        else PJ_COL(16);
+#undef PJ_COL
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
 }
