@@ -61,6 +61,10 @@ typedef enum {
 /* Arithmetic of the reduced contraction.  Inputs and outputs are FP64 for
  * PJ_F64 and FP32 for every other mode; projections are computed in FP32
  * (FP64 for PJ_F64) and rounded to the mode's operand format.
+ *   PJ_F32  : FP32 operands and accumulation; larger outputs contract on the
+ *             BF16 matrix cores with every operand as the exact sum of three
+ *             BF16 values (six exact products; tiles holding values such a sum
+ *             cannot carry use the FP32 instructions);
  *   PJ_BF16 / PJ_F16   : one rounded operand, FP32 accumulation;
  *   PJ_BF16X3 / PJ_F16X3: x = hi + lo split, R = hi*hi + hi*lo + lo*hi,
  *                         FP32 accumulation (about FP32-level error);

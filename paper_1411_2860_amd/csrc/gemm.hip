@@ -760,13 +760,214 @@ __device__ __forceinline__ void gemm_tile_dma_ra(
     store_tile<PREC, WM, WN>(acc, lane, rb0, cb0, P, Q, R, ldr, beta);
 }
 
+// FP32 on the BF16 matrix cores.  An FP32 value is the exact sum of three
+// BF16 values h + m + l (8 significant bits each, round to nearest), and
+// a b = h h' + (h m' + m h') + (m m' + h l' + l h') up to terms below 2^-26
+// |a b|: six BF16 products, every one exact, accumulated in FP32.  The BF16
+// instructions do 16 times the work of the FP32 ones per cycle, so six of them
+// still run 2.7 times as fast, with fewer roundings of the accumulator (one per
+// instruction of 16 indices instead of one per index).  Error against FP64
+// measured at 0.4 .. 0.9 of the FP32 instructions' (image, normal, positive and
+// log-normal operands, 1 to 64 of 64 projections).  Bound by the BF16 matrix
+// pipe, which sustains about 1.3 PFLOP/s here: 1024 x 8192 outputs, contraction
+// 4096: 341 us = 1.21 PFLOP/s of BF16 products (482 us on the FP32
+// instructions), contraction 1024: 92.6 us (127 us).
+//
+// The packed operands stay FP32.  Per stage of KS x 16 indices each wave loads
+// its share of the workgroup's tiles into registers two stages ahead (two FP32
+// tiles of 8 indices make one 16-index fragment; the order of the indices
+// within it is the same for both operands), splits them once for the whole
+// workgroup, and parks the three planes in the other of two LDS buffers while
+// the matrix cores work on this one.
+//
+// Values the split cannot carry go another way: infinities, NaN and values that
+// round to a BF16 infinity leave a NaN in the products they reach; values below
+// 2^-102 (whose l would fall off the BF16 range) are noted while splitting.  A
+// workgroup that sees either in the rows and columns it stores computes its
+// tile again with the FP32 instructions.
+constexpr unsigned kSplitTiny = (127u - 102u) << 24;      // 2^-102, shifted left by the sign bit
+
+__device__ __forceinline__ void split3(const f32x4& u, const f32x4& v, bf16x8 (&o)[3], unsigned& least)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float x = e < 4 ? u[e & 3] : v[e & 3];
+        const __bf16 h = (__bf16)x;
+        const float r = x - (float)h;
+        const __bf16 m = (__bf16)r;
+        o[0][e] = h;
+        o[1][e] = m;
+        o[2][e] = (__bf16)(r - (float)m);
+        const unsigned w = (__float_as_uint(x) << 1) - 1u;    // zero becomes the largest value
+        least = w < least ? w : least;
+    }
+}
+
+template <int WM, int WN, int WAVES_M, int WAVES_N>
+constexpr int gemm_split_ks()
+{
+    constexpr int nt = WM * WAVES_M + WN * WAVES_N;
+    return nt >= 12 || nt <= 4 || nt % (WAVES_M * WAVES_N) != 0 ? 2 : 1;
+}
+
+template <int WM, int WN, int WAVES_M, int WAVES_N>
+__device__ __forceinline__ void gemm_tile_split(
+    const char* __restrict__ X, int64_t x_nrb, int64_t x_nkb, const char* __restrict__ Y, int64_t y_nrb,
+    int64_t y_nkb, int64_t nkb, int64_t kb_lo, int64_t P, int64_t Q, float* __restrict__ R, int64_t ldr, float beta,
+    int64_t tm, int64_t tn)
+{
+    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int BMB = WM * WAVES_M, BNB = WN * WAVES_N, NT = BMB + BNB;
+    constexpr int KS = gemm_split_ks<WM, WN, WAVES_M, WAVES_N>();
+    constexpr int PER_W = NT * KS / NW;            // 16-index fragments split per wave and stage
+    constexpr int STAGE = NT * KS * 3 * 64;        // 16-byte chunks of a stage
+    static_assert(NT * KS % NW == 0, "every wave splits the same number of fragments");
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    bf16x8* lds = reinterpret_cast<bf16x8*>(smem_raw);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+    const int64_t rbB = tm * BMB, cbB = tn * BNB;
+
+    const char* src[PER_W];
+    bool live[PER_W];                              // the lane's row is one the tile stores
+    unsigned least[PER_W];
+#pragma unroll
+    for (int i = 0; i < PER_W; ++i) {
+        const int blk = (wave + i * NW) % NT;
+        const int64_t base = nkb > 0 ? kb_lo : 0;
+        if (blk < BMB) {
+            const int64_t rb = rbB + blk;
+            src[i] = X + ((rb < x_nrb ? rb : 0) * x_nkb + base) * 1024;
+            live[i] = rb * 32 + (lane & 31) < P;
+        } else {
+            const int64_t cb = cbB + blk - BMB;
+            src[i] = Y + ((cb < y_nrb ? cb : 0) * y_nkb + base) * 1024;
+            live[i] = cb * 32 + (lane & 31) < Q;
+        }
+        least[i] = ~0u;
+    }
+    // stage st holds the 16-index blocks n16 - 1 - st KS - kk, highest first;
+    // FP32 tiles past either end read tile 0 and count as zero
+    const int nk = (int)nkb;
+    const int n16 = (nk + 1) / 2;
+    const int nst = (n16 + KS - 1) / KS;
+    struct Raw { f32x4 t[PER_W][2]; };
+    auto gload = [&](int st, Raw& r) {
+#pragma unroll
+        for (int i = 0; i < PER_W; ++i) {
+            const int kb = 2 * (n16 - 1 - st * KS - (wave + i * NW) / NT);
+            const int k0 = kb < 0 ? 0 : kb, k1 = kb < 0 || kb + 1 >= nk ? 0 : kb + 1;
+            r.t[i][0] = *reinterpret_cast<const f32x4*>(src[i] + (int64_t)k0 * 1024 + lane * 16);
+            r.t[i][1] = *reinterpret_cast<const f32x4*>(src[i] + (int64_t)k1 * 1024 + lane * 16);
+        }
+    };
+    auto park = [&](int st, int buf, Raw& r) {
+#pragma unroll
+        for (int i = 0; i < PER_W; ++i) {
+            const int u = wave + i * NW;
+            const int kb = 2 * (n16 - 1 - st * KS - u / NT);
+            const int m0 = kb < 0 ? 0 : -1, m1 = kb < 0 || kb + 1 >= nk ? 0 : -1;     // zero by a mask, not a branch
+            const f32x4 a = __builtin_bit_cast(f32x4, __builtin_bit_cast(i32x4, r.t[i][0]) & m0);
+            const f32x4 b = __builtin_bit_cast(f32x4, __builtin_bit_cast(i32x4, r.t[i][1]) & m1);
+            bf16x8 o[3];
+            split3(a, b, o, least[i]);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) lds[buf * STAGE + (u * 3 + pl) * 64 + lane] = o[pl];
+        }
+    };
+    f32x16 acc[WM][WN];
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int b = 0; b < WN; ++b)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[a][b][j] = 0.0f;
+    auto contract = [&](int buf) {
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            const bf16x8* base = lds + buf * STAGE + kk * NT * 3 * 64 + lane;
+            bf16x8 fa[WM][3], fb[WN][3];
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+#pragma unroll
+                for (int a = 0; a < WM; ++a) fa[a][pl] = base[((wm * WM + a) * 3 + pl) * 64];
+#pragma unroll
+                for (int b = 0; b < WN; ++b) fb[b][pl] = base[((BMB + wn * WN + b) * 3 + pl) * 64];
+            }
+            // smallest products first
+            constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int a = 0; a < WM; ++a)
+#pragma unroll
+                    for (int b = 0; b < WN; ++b)
+                        acc[a][b] =
+                            __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a][pa[q]], fb[b][pb[q]], acc[a][b], 0, 0, 0);
+        }
+    };
+    Raw r0, r1;
+    gload(0, r0);
+    gload(1, r1);
+    park(0, 0, r0);
+    __syncthreads();
+    // stage st in buffer st & 1; stage st + 1 is in registers, st + 2 on its way
+    auto step = [&](int st, int buf, Raw& next, Raw& far) {
+        gload(st + 2, far);
+        __builtin_amdgcn_sched_barrier(0);
+        contract(buf);
+        park(st + 1, buf ^ 1, next);
+        __syncthreads();
+    };
+    int st = 0;
+    for (; st + 1 < nst; st += 2) {
+        step(st, 0, r1, r0);
+        step(st + 1, 1, r0, r1);
+    }
+    if (st < nst) {
+        contract(0);
+        __syncthreads();
+    }
+    // does the tile hold a value the split could not carry?
+    const int64_t rb0 = rbB + wm * WM, cb0 = cbB + wn * WN;
+    float z = 0.0f;
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int b = 0; b < WN; ++b)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                int row, col;
+                acc_pos<32>(j, lane, row, col);
+                if ((rb0 + a) * 32 + row < P && (cb0 + b) * 32 + col < Q) z = fmaf(acc[a][b][j], 0.0f, z);
+            }
+    bool bad = z != z;
+#pragma unroll
+    for (int i = 0; i < PER_W; ++i) bad |= live[i] && least[i] < kSplitTiny - 1u;
+    int* flag = reinterpret_cast<int*>(smem_raw);
+    const bool wbad = __builtin_amdgcn_ballot_w64(bad) != 0;
+    if (lane == 0) flag[wave] = wbad;
+    __syncthreads();
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) any |= flag[w];
+    __syncthreads();                               // the flags are read before a next item's first stage
+    if (__builtin_amdgcn_readfirstlane(any))
+        gemm_tile<P_F32, WM, WN, WAVES_M, WAVES_N>(X, x_nrb, x_nkb, 0, 0, Y, y_nrb, y_nkb, 0, 0, nkb, kb_lo, P, Q, R,
+                                                   ldr, beta, tm, tn);
+    else
+        store_tile<P_F32, WM, WN>(acc, lane, rb0, cb0, P, Q, R, ldr, beta);
+}
+
 // Kernel body selector: KIND 0 = direct fragment loads, 1 = LDS-staged with
 // loads two steps ahead, 2 = LDS-staged with loads four steps ahead, 3 = LDS
 // ring filled by direct global-to-LDS copies, 4 = the same ring with the
 // fragments read one step ahead, 5 = kind 4 with the step's copies issued
 // first and its fragment reads interleaved one by one with its matrix
 // instructions (scheduling groups), so that the LDS command queue never
-// holds a whole step's reads in front of the matrix pipe.
+// holds a whole step's reads in front of the matrix pipe, 6 = FP32 split into
+// three BF16 values (the other formats run it as kind 1).
 template <int KIND, int PREC, int WM, int WN, int WAVES_M, int WAVES_N>
 __device__ __forceinline__ void gemm_any(
     const char* __restrict__ X, int64_t x_nrb, int64_t x_nkb, int64_t x_plane, int64_t x_pb,
@@ -774,7 +975,10 @@ __device__ __forceinline__ void gemm_any(
     int64_t nkb, int64_t kb_lo, int64_t P, int64_t Q, typename MT<PREC>::out_t* __restrict__ R, int64_t ldr,
     float beta, int64_t tm, int64_t tn)
 {
-    if constexpr (KIND == 5 && sizeof(typename MT<PREC>::frag) == 16)
+    if constexpr (KIND == 6 && PREC == P_F32)
+        gemm_tile_split<WM, WN, WAVES_M, WAVES_N>(X, x_nrb, x_nkb, Y, y_nrb, y_nkb, nkb, kb_lo, P, Q, R, ldr, beta, tm,
+                                                  tn);
+    else if constexpr (KIND == 5 && sizeof(typename MT<PREC>::frag) == 16)
         gemm_tile_dma_ra<PREC, WM, WN, WAVES_M, WAVES_N, 4, gemm_lds_ks<PREC, WM, WN, WAVES_M, WAVES_N>(), true>(
             X, x_nrb, x_nkb, x_plane, Y, y_nrb, y_nkb, y_plane, nkb, kb_lo, P, Q, R, ldr, beta, tm, tn);
     else if constexpr (KIND == 4 && sizeof(typename MT<PREC>::frag) == 16)
@@ -795,7 +999,9 @@ __device__ __forceinline__ void gemm_any(
 template <int KIND, int PREC, int WM, int WN, int WAVES_M, int WAVES_N>
 constexpr size_t gemm_lds_bytes()
 {
-    if constexpr (KIND >= 3 && sizeof(typename MT<PREC>::frag) == 16)
+    if constexpr (KIND == 6 && PREC == P_F32)
+        return 2ull * gemm_split_ks<WM, WN, WAVES_M, WAVES_N>() * (WM * WAVES_M + WN * WAVES_N) * 3 * 1024;
+    else if constexpr (KIND >= 3 && KIND <= 5 && sizeof(typename MT<PREC>::frag) == 16)
         return 4ull * gemm_lds_ks<PREC, WM, WN, WAVES_M, WAVES_N>() * (WM * WAVES_M + WN * WAVES_N) *
                MT<PREC>::PLANES * 1024;
     else if constexpr (KIND >= 1 && sizeof(typename MT<PREC>::frag) == 16)
@@ -1087,7 +1293,7 @@ int launch_gemm_t(const GemmArgs& a, hipStream_t s)
 
 }  // namespace
 
-// Tile configurations: (kind: 0 direct fragment loads, 1 - 5 LDS-staged; MFMA
+// Tile configurations: (kind: 0 direct fragment loads, 1 - 6 LDS-staged; MFMA
 // blocks per wave along M, along N; waves along M, along N; minimum resident
 // workgroups per CU).  The workgroup tile is RB*WM*WAVES_M x RB*WN*WAVES_N.
 // FP8 runs the LDS kinds as direct.
@@ -1110,7 +1316,9 @@ int launch_gemm_t(const GemmArgs& a, hipStream_t s)
     X(15, 2, 2, 2, 4, 2, 1)  \
     X(16, 4, 2, 2, 4, 2, 1)  \
     X(17, 4, 2, 2, 2, 2, 2)  \
-    X(18, 5, 2, 2, 4, 2, 1)
+    X(18, 5, 2, 2, 4, 2, 1)  \
+    X(19, 6, 1, 2, 4, 2, 1)  \
+    X(20, 6, 2, 2, 4, 2, 1)
 
 namespace {
 struct TileCfg { int wm, wn, wavm, wavn; };
@@ -1205,14 +1413,24 @@ int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb)
 {
     // small problems: smaller tiles so that the grid still covers the chip
     const int64_t tiles128 = cdiv(P, 128) * cdiv(Q, 128);
+    if (prec == P_F32) {
+        // The split 128 x 128 tile (one workgroup a CU holds its rate) from
+        // more tiles than half the CUs: 1003 x 3001, 102 k-blocks (192 tiles) 51.5 ->
+        // 38.7 us, 2048 x 2048, 128 k-blocks (256 tiles) 80 -> 53 us; at 128 tiles and
+        // below the 64 x 64 tile has more CUs at work (4096 x 512, 512 k-blocks: 150
+        // against 156 us; 512 x 2048, 128 k-blocks: 23.9 against 42.8 us).  256 x 128 where
+        // those tiles cover the chip and a contraction of 64 k-blocks pays for
+        // its longer first stage (1024 x 8192: 16 k-blocks 21.1 against 20.0 us, 32: 30.0
+        // and 30.0, 64: 51.9 and 52.8, 128: 92.6 and 97.6, 512: 341 and 366; the FP32
+        // instructions need 25.6, 41, 75, 127 and 482 us).
+        if (tiles128 <= 128) return 5;
+        return cdiv(P, 256) * cdiv(Q, 128) >= 256 && nkb >= 64 ? 20 : 19;
+    }
     if (tiles128 < 256) return 5;
     // (measured on the recognition and backward shapes, one timing per config)
     const bool fill256 = cdiv(P, 256) * cdiv(Q, 128) >= 256;   // 256 x 128 tiles still cover the chip
     switch (prec) {
     case P_F64: return 10;                                 // LDS, 8 waves, 128 x 64 (16 x 16 blocks)
-    case P_F32:
-        if (!fill256) return 0;
-        return nkb >= 16 ? 18 : 10;                        // copy ring read ahead, interleaved; very short: LDS 8 waves
     case P_FP8:
     case P_FP8X2: return 9;                                // 128 x 256, 8 waves, fragments direct
     case P_BF16X3:
@@ -1231,14 +1449,15 @@ int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb)
 // call: BF16x3 1042 -> 843 us and BF16 765 -> 648 us against the direct
 // 128 x 128 tile of before; 128 x 128 rings 855 and 670; r = 16 BF16x3
 // contraction 3.54 -> 1.66 ms; up to sides of 512 the choice does not matter,
-// up to 2048 it is 251 -> 230 us).  FP32: the same ring on 128 x 128 tiles, two workgroups
-// a CU (1785 -> 1522 us; 256 x 128 interleaved 1604).  FP64 and FP8 have no
-// ring: direct 128 x 128 blocks.
+// up to 2048 it is 251 -> 230 us).  FP32: the split tile of 256 x 128
+// (r = 1 / 4 / 16: 629 / 1200 / 3800 us, 128 x 128: 672 / 1350 / 4210, the rings on
+// the FP32 instructions 697 / 1540 / 4930, the direct tile of before 1785 us at
+// r = 4).  FP64 and FP8 have no ring: direct 128 x 128 blocks.
 int gemm_grouped_default_config(int prec)
 {
     switch (prec) {
     case P_BF16: case P_BF16X3: case P_F16: case P_F16X3: return 16;
-    case P_F32: return 17;
+    case P_F32: return 20;
     default: return 0;
     }
 }
