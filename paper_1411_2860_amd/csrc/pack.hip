@@ -893,8 +893,34 @@ int launch_t(const PackArgs* a, int n, hipStream_t s)
 }
 
 template <typename TIn, int PREC>
+int launch_colpack(const PackArgs* a, int n, hipStream_t s);
+template <typename TIn, int PREC>
+bool col_route(const PackArgs& a);
+
+template <typename TIn, int PREC>
 int launch_p(const PackArgs* a, int n, hipStream_t s)
 {
+    bool ca = col_route<TIn, PREC>(a[0]), cb = n > 1 && col_route<TIn, PREC>(a[1]);
+    // Two sides the tile packer takes in one launch, or one side alone, go by
+    // columns from 4 MB of transposed source: below that a second launch, or the
+    // pass of one thread over all L indices, costs more than the tiles do (64 x
+    // 818 on both sides: 8.0 us by tiles, 10.8 us by columns; 256 x 256 FP64, one side
+    // transposed: 7.1 us in one launch, 11.2 us in two; 2101 x 3001: 27.7 against 13.8 us).
+    // Sides that need a launch each anyway always do (296 x 128 and 128 x 173: whole
+    // call 28 -> 20 us).
+    if (ca || cb) {
+        const double bytes = (ca ? (double)a[0].P * a[0].K : 0.0) + (cb ? (double)a[1].P * a[1].K : 0.0);
+        if (bytes * sizeof(TIn) < 4e6 &&
+            (n == 1 || std::is_same<TIn, double>::value ||
+             job_layout(make_job<TIn, PREC>(a[0])) == job_layout(make_job<TIn, PREC>(a[1]))))
+            ca = cb = false;
+    }
+    if (ca && (n == 1 || cb)) return launch_colpack<TIn, PREC>(a, n, s);
+    if (ca || cb) {
+        // one side by columns, the other by tiles
+        const int e = launch_colpack<TIn, PREC>(ca ? a : a + 1, 1, s);
+        return e != 0 ? e : launch_p<TIn, PREC>(ca ? a + 1 : a, 1, s);
+    }
     int r = a[0].r;
     if (n > 1 && a[1].r > r) r = a[1].r;
     if (r == 1) return launch_t<TIn, PREC, 1, 1>(a, n, s);
@@ -931,124 +957,173 @@ struct ColJob {
     const TIn* coef;        // L x L, element (t, l)
     char* out;
     int64_t nkb, Gp, plane_stride;
-    int64_t ncol;           // column tiles
     TIn* keep; int64_t keep_ld;
+    int TC;                 // > 0: sums in the tile packer's matrix-core order with rounds of TC
+                            // indices (col_order); 0: ascending
 };
+
+// Index within a round of TC (a multiple of 4) that the tile packer's matrix
+// cores add at place u: they run over blocks of 16 indices, in block q over
+// e = 0 .. 3, each instruction adding indices 16 q + 4 kq + e of its (up to four)
+// chunks kq one after the other.
+__host__ __device__ constexpr int col_order(int u, int TC)
+{
+    const int b = u & ~15, j = u - b;
+    const int c = TC - b >= 16 ? 4 : (TC - b) / 4;
+    return c == 4 ? b + ((j & 3) << 2) + (j >> 2) : b + 4 * (j % c) + j / c;
+}
 
 // RL projections at a time (1, 2, 4, 8 or 16: no more than r needs, so that
 // few projections leave the registers to loads in flight): the rows of
-// col_depth<RL>() - 1 further indices t, E groups each, are on their way while
-// one index is accumulated.  24 problems, r = 4 (547 MB read, 145 MB written):
+// col_depth<RL, EW>() indices t, EW groups each, are on their way at a time.  SPLIT = 1: a thread holds a whole lane vector
+// (EW = E groups) of one of 256 columns.  SPLIT > 1: SPLIT threads share the
+// lane vector of one of 256 / SPLIT columns and put it together through LDS,
+// for sources that would otherwise leave most of the chip without a workgroup.
+// 24 problems, r = 4 (547 MB read, 145 MB written):
 // 203 -> 176 us against 16 projections at a time in tiles of two lane vectors.
-template <int RL> constexpr int col_depth() { return RL <= 4 ? 4 : 2; }
+template <int RL, int EW>
+constexpr int col_depth() { return RL * EW <= 32 ? 4 : 2; }
 
-template <typename TIn, int PREC, int RL>
+template <typename TIn, int PREC, int RL, int SPLIT>
 __device__ __forceinline__ void colpack_tile(const ColJob<TIn>& J, int64_t tix)
 {
     constexpr Layout ly = layout_of(PREC);
     constexpr int KB = ly.KB, RB = ly.RB, E = ly.E;
-    constexpr int D = col_depth<RL>();
-    static_assert(KB % E == 0 && E <= 8, "lane vectors of at most 8 values");
-    __shared__ TIn cs[kColMaxL * RL];       // coefficients of the pass: [t][l - l0]
-    const int64_t ct = tix % J.ncol, gv = tix / J.ncol;      // column tile, lane vector of groups
-    const int64_t p = ct * kColW + threadIdx.x;
+    constexpr int CW = kColW / SPLIT, EW = E / SPLIT;       // columns a workgroup, groups a thread
+    constexpr int D = col_depth<RL, EW>();
+    static_assert(KB % E == 0 && E <= 8 && E % SPLIT == 0, "lane vectors of at most 8 values");
+    __shared__ TIn cs[kColMaxL * RL];       // coefficients of the pass, in the order of the sums: [i][l - l0]
+    const int TC = J.TC;
+    const int64_t ncol = (J.P + CW - 1) / CW;
+    const int64_t ct = tix % ncol, gv = tix / ncol;          // column tile, lane vector of groups
+    const int cl = threadIdx.x % CW;
+    const int gs = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / CW) : 0;
+    const int64_t p = ct * CW + cl;
     const int64_t j0 = gv * E / KB * KB;
     const int g0 = (int)(gv * E - j0);
     const int L = J.L, r = J.r;
     const bool live = p < J.P;
-    const TIn* __restrict__ base = J.X + ct * kColW;
+    const TIn* __restrict__ base = J.X + ct * CW;
     // byte offset of the lane's column; reads stay inside the source
-    const unsigned col = (live ? threadIdx.x : (unsigned)(J.P - 1 - ct * kColW)) * (unsigned)sizeof(TIn);
+    const unsigned col = (live ? (unsigned)cl : (unsigned)(J.P - 1 - ct * CW)) * (unsigned)sizeof(TIn);
     for (int l0 = 0; l0 < r; l0 += RL) {
         __syncthreads();
         for (int x = threadIdx.x; x < L * RL; x += kColW) {
-            const int t = x / RL, lq = x % RL;
+            const int i = x / RL, lq = x % RL;
+            const int t = TC > 0 ? i / TC * TC + col_order(i % TC, TC) : i;
             cs[x] = l0 + lq < r ? J.coef[(int64_t)t * L + l0 + lq] : (TIn)0;
         }
         __syncthreads();
-        TIn acc[RL][E];
+        TIn acc[RL][EW];
 #pragma unroll
         for (int q = 0; q < RL; ++q)
 #pragma unroll
-            for (int e = 0; e < E; ++e) acc[q][e] = (TIn)0;
+            for (int e = 0; e < EW; ++e) acc[q][e] = (TIn)0;
         // Row addresses are wave-uniform, the column a 32-bit lane offset: a
         // load is one scalar addition and no vector work.  The row address
         // is opaque to the compiler, which otherwise forms per-lane addresses
         // of the whole loop ahead of it (198 registers, two waves per SIMD).
-        const int64_t k0 = (j0 + g0) * L;
-        auto fma = [&](int t, const TIn (&x)[E]) {
+        const int64_t k0 = (j0 + g0 + gs * EW) * L;
+        auto fma = [&](int t, const TIn (&x)[EW]) {
             const TIn* c = cs + t * RL;
 #pragma unroll
-            for (int e = 0; e < E; ++e)
+            for (int e = 0; e < EW; ++e)
 #pragma unroll
                 for (int q = 0; q < RL; ++q) acc[q][e] += c[q] * x[e];
         };
-        // whole lane vectors, and the loads ahead of them, inside the source;
-        // vectors of padding groups (past K) stay zero
+        // groups inside the source; padding groups (past K) stay zero
         if (k0 >= J.K) {
-        } else if (k0 + (int64_t)E * L + D <= J.K) {
+        } else if (k0 + (int64_t)EW * L <= J.K && L >= D) {
             const char* row = reinterpret_cast<const char*>(base + k0 * J.ld);
             const int64_t step = J.ld * (int64_t)sizeof(TIn), estep = step * L;
-            auto ld = [&](TIn (&x)[E]) {
+            int u0 = 0, u = 0;                   // next place of the sums: round and place in it
+            auto ld = [&](TIn (&x)[EW]) {
                 const char* q = row;
+                if (TC > 0) {
+                    q += (int64_t)(u0 + col_order(u, TC)) * step;
+                    if (++u == TC) {
+                        u0 += TC;
+                        u = 0;
+                    }
+                } else {
+                    row += step;
+                }
 #pragma unroll
-                for (int e = 0; e < E; ++e, q += estep) {
-                    uintptr_t u = (uintptr_t)q;
-                    asm volatile("" : "+s"(u));
+                for (int e = 0; e < EW; ++e, q += estep) {
+                    uintptr_t a = (uintptr_t)q;
+                    asm volatile("" : "+s"(a));
                     using GB = const __attribute__((address_space(1))) char;
                     using GT = const __attribute__((address_space(1))) TIn;
-                    x[e] = *(GT*)((GB*)u + col);
+                    x[e] = *(GT*)((GB*)a + col);
                 }
-                row += step;
             };
-            TIn x[D][E];
+            // D indices in flight, none past L
+            TIn x[D][EW];
 #pragma unroll
-            for (int d = 0; d + 1 < D; ++d) ld(x[d]);
+            for (int d = 0; d < D; ++d) ld(x[d]);
             int t = 0;
-            for (; t + D <= L; t += D) {
+            for (; t + 2 * D <= L; t += D) {
 #pragma unroll
                 for (int d = 0; d < D; ++d) {
-                    ld(x[(d + D - 1) % D]);
                     fma(t + d, x[d]);
+                    ld(x[d]);
                 }
             }
 #pragma unroll
-            for (int d = 0; d + 1 < D; ++d)
-                if (t + d < L) fma(t + d, x[d]);
-        } else {
-            for (int t = 0; t < L; ++t) {
-                TIn x[E];
+            for (int d = 0; d < D; ++d) {
+                fma(t + d, x[d]);
+                if (t + D + d < L) ld(x[d]);
+            }
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
+            for (int d = 0; d + 1 < D; ++d)
+                if (t + D + d < L) fma(t + D + d, x[d]);
+        } else {
+            for (int i = 0; i < L; ++i) {
+                const int t = TC > 0 ? i / TC * TC + col_order(i % TC, TC) : i;
+                TIn x[EW];
+#pragma unroll
+                for (int e = 0; e < EW; ++e) {
                     const int64_t k = k0 + (int64_t)e * L + t;
                     const char* q = reinterpret_cast<const char*>(base + (k < J.K ? k : J.K - 1) * J.ld);
                     const TIn v = *reinterpret_cast<const TIn*>(q + col);
                     x[e] = k < J.K ? v : (TIn)0;
                 }
-                fma(t, x);
+                fma(i, x);
             }
         }
-        if (live) {
-            const int64_t rb = p / RB;
-            const int rib = (int)(p % RB), g = g0 / E;
+        auto put = [&](int q, const TIn (&v)[E]) {
+            const int l = l0 + q;
+            if (l >= r || !live) return;
+            const int64_t kb = ((int64_t)l * J.Gp + j0) / KB;
+            const int64_t off = ((p / RB * J.nkb + kb) * 64 + g0 / E * RB + p % RB) * (int64_t)ly.LB;
+            store_lane<PREC, E, TIn>(J.out, off, J.plane_stride, 0, v);
+            if (J.keep) {
+                TIn* dst = J.keep + p * J.keep_ld + (int64_t)l * J.Gp + j0 + g0;
 #pragma unroll
-            for (int q = 0; q < RL; ++q) {
-                const int l = l0 + q;
-                if (l >= r) break;
-                const int64_t kb = ((int64_t)l * J.Gp + j0) / KB;
-                const int64_t off = ((rb * J.nkb + kb) * 64 + g * RB + rib) * (int64_t)ly.LB;
-                store_lane<PREC, E, TIn>(J.out, off, J.plane_stride, 0, acc[q]);
-                if (J.keep) {
-                    TIn* dst = J.keep + p * J.keep_ld + (int64_t)l * J.Gp + j0 + g0;
+                for (int e = 0; e < E; ++e) dst[e] = v[e];
+            }
+        };
+        if constexpr (SPLIT == 1) {
 #pragma unroll
-                    for (int e = 0; e < E; ++e) dst[e] = acc[q][e];
-                }
+            for (int q = 0; q < RL; ++q) put(q, acc[q]);
+        } else {
+            __shared__ TIn xs[RL * E * CW];                  // [projection][group][column]
+#pragma unroll
+            for (int q = 0; q < RL; ++q)
+#pragma unroll
+                for (int e = 0; e < EW; ++e) xs[(q * E + gs * EW + e) * CW + cl] = acc[q][e];
+            __syncthreads();
+            for (int q = gs; q < RL; q += SPLIT) {
+                TIn v[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[e] = xs[(q * E + e) * CW + cl];
+                put(q, v);
             }
         }
     }
 }
 
-template <typename TIn, int PREC, int RL>
+template <typename TIn, int PREC, int RL, int SPLIT>
 __global__ __launch_bounds__(kColW) void colpack_grouped_kernel(const ColJob<TIn>* __restrict__ jobs,
                                                                const int64_t* __restrict__ prefix, int njobs)
 {
@@ -1064,13 +1139,22 @@ __global__ __launch_bounds__(kColW) void colpack_grouped_kernel(const ColJob<TIn
     j.coef = global_ptr(j.coef);
     j.out = global_ptr(j.out);
     j.keep = global_ptr(j.keep);
-    colpack_tile<TIn, PREC, RL>(j, b - prefix[lo]);
+    colpack_tile<TIn, PREC, RL, SPLIT>(j, b - prefix[lo]);
+}
+
+// One or two jobs passed by value.
+template <typename TIn, int PREC, int RL, int SPLIT>
+__global__ __launch_bounds__(kColW) void colpack_kernel(ColJob<TIn> ja, ColJob<TIn> jb, int64_t nblk_a)
+{
+    if ((int64_t)blockIdx.x < nblk_a) colpack_tile<TIn, PREC, RL, SPLIT>(ja, (int64_t)blockIdx.x);
+    else colpack_tile<TIn, PREC, RL, SPLIT>(jb, (int64_t)blockIdx.x - nblk_a);
 }
 
 template <typename TIn, int PREC>
-ColJob<TIn> make_coljob(const PackArgs& a)
+ColJob<TIn> make_coljob(const PackArgs& a, int TC = 0)
 {
     ColJob<TIn> j;
+    j.TC = TC;
     j.X = (const TIn*)a.X;
     j.ld = a.ld;
     j.P = a.P;
@@ -1082,7 +1166,6 @@ ColJob<TIn> make_coljob(const PackArgs& a)
     j.nkb = a.geom.nkb;
     j.Gp = a.geom.Gp;
     j.plane_stride = a.geom.plane_bytes + a.geom.scale_plane;
-    j.ncol = cdiv(a.P, kColW);
     j.keep = (TIn*)a.keep;
     j.keep_ld = a.keep_ld;
     return j;
@@ -1092,6 +1175,30 @@ ColJob<TIn> make_coljob(const PackArgs& a)
 template <int PREC>
 constexpr bool colpack_ok() { return layout_of(PREC).E <= 8; }
 
+// Workgroups of a source with `split` threads a lane vector.  Below kColFill (one
+// and a half a CU) for whole lane vectors, these are shared by col_split()
+// threads: 128 workgroups (4096 x 4096, L = 64, r = 8) 71.6 -> 30 us; 408 (2101 x 3001,
+// L = 16, r = 6) 13.8 against 15.2 us shared.
+constexpr int64_t kColFill = 384;
+template <int PREC>
+constexpr int col_split() { return layout_of(PREC).E < 4 ? layout_of(PREC).E : 4; }
+template <int PREC>
+int64_t col_blocks(const PackArgs& a, int split)
+{
+    return cdiv(a.P, kColW / split) * (a.geom.Gp / layout_of(PREC).E);
+}
+
+// LAUNCH(RL, SPLIT) for the projections `r` and the sharing `sp`.
+#define PJ_COL_DISPATCH(LAUNCH)                                                \
+    do {                                                                       \
+        constexpr int kSp = col_split<PREC>();                                 \
+        if (r == 1) { if (sp == 1) LAUNCH(1, 1); else LAUNCH(1, kSp); }        \
+        else if (r == 2) { if (sp == 1) LAUNCH(2, 1); else LAUNCH(2, kSp); }   \
+        else if (r <= 4) { if (sp == 1) LAUNCH(4, 1); else LAUNCH(4, kSp); }   \
+        else if (r <= 8) { if (sp == 1) LAUNCH(8, 1); else LAUNCH(8, kSp); }   \
+        else { if (sp == 1) LAUNCH(16, 1); else LAUNCH(16, kSp); }             \
+    } while (0);
+
 template <typename TIn, int PREC>
 int launch_colpack_grouped(const PackArgs* a, int n, char* jobs_at, char* prefix_at, hipStream_t s)
 {
@@ -1100,29 +1207,71 @@ int launch_colpack_grouped(const PackArgs* a, int n, char* jobs_at, char* prefix
     } else {
         std::vector<ColJob<TIn>> jobs(n);
         std::vector<int64_t> prefix(n + 1, 0);
+        int r = 1;
+        int64_t whole = 0;
         for (int i = 0; i < n; ++i) {
             jobs[i] = make_coljob<TIn, PREC>(a[i]);
-            prefix[i + 1] = prefix[i] + jobs[i].ncol * (a[i].geom.Gp / layout_of(PREC).E);
+            r = a[i].r > r ? a[i].r : r;
+            whole += col_blocks<PREC>(a[i], 1);
         }
+        const int sp = whole < kColFill ? col_split<PREC>() : 1;
+        for (int i = 0; i < n; ++i) prefix[i + 1] = prefix[i] + col_blocks<PREC>(a[i], sp);
         if (prefix[n] == 0) return 0;
         if (prefix[n] > 0x7fffffff) return -2;
         if (hipMemcpyAsync(jobs_at, jobs.data(), sizeof(ColJob<TIn>) * n, hipMemcpyHostToDevice, s) != hipSuccess ||
             hipMemcpyAsync(prefix_at, prefix.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, s) !=
                 hipSuccess)
             return -1;
-        int r = 1;
-        for (int i = 0; i < n; ++i) r = a[i].r > r ? a[i].r : r;
-#define PJ_COL(RL_)                                                                                            \
-    hipLaunchKernelGGL((colpack_grouped_kernel<TIn, PREC, RL_>), dim3((unsigned)prefix[n]), dim3(kColW), 0, s, \
+#define PJ_COL(RL_, SP_)                                                                                  \
+    hipLaunchKernelGGL((colpack_grouped_kernel<TIn, PREC, RL_, SP_>), dim3((unsigned)prefix[n]), dim3(kColW), 0, s, \
                        (const ColJob<TIn>*)jobs_at, (const int64_t*)prefix_at, n)
-        if (r == 1) PJ_COL(1);
-        else if (r == 2) PJ_COL(2);
-        else if (r <= 4) PJ_COL(4);
-        else if (r <= 8) PJ_COL(8);
-        else PJ_COL(16);
+        PJ_COL_DISPATCH(PJ_COL)
 #undef PJ_COL
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
+}
+
+// Column-wise launch of one or two transposed sources with the tile packer's
+// sums (same order, so the packed bytes are the same): the matrix-core order
+// where the tile packer would use them (more than one projection, FP32 input).
+template <typename TIn, int PREC>
+int launch_colpack(const PackArgs* a, int n, hipStream_t s)
+{
+    if constexpr (!colpack_ok<PREC>()) {
+        return -2;
+    } else {
+        ColJob<TIn> j[2];
+        int64_t nb[2] = {0, 0}, whole = 0;
+        int r = 1;
+        for (int i = 0; i < n; ++i) {
+            r = a[i].r > r ? a[i].r : r;
+            whole += col_blocks<PREC>(a[i], 1);
+        }
+        const int sp = whole < kColFill ? col_split<PREC>() : 1;
+        for (int i = 0; i < n; ++i) {
+            j[i] = make_coljob<TIn, PREC>(a[i], r > 1 && pack_mfma<TIn, PREC, 4, 1>() ? make_job<TIn, PREC>(a[i]).TC : 0);
+            nb[i] = col_blocks<PREC>(a[i], sp);
+        }
+        if (n < 2) j[1] = j[0];
+        if (nb[0] + nb[1] > 0x7fffffff) return -2;
+#define PJ_COL(RL_, SP_)                                                                                          \
+    hipLaunchKernelGGL((colpack_kernel<TIn, PREC, RL_, SP_>), dim3((unsigned)(nb[0] + nb[1])), dim3(kColW), 0, s, \
+                       j[0], j[1], nb[0])
+        PJ_COL_DISPATCH(PJ_COL)
+#undef PJ_COL
+        return hipGetLastError() == hipSuccess ? 0 : -1;
+    }
+}
+
+// Whether a transposed source goes column-wise in a launch of its own: rounds
+// of whole chunks (the order of the sums is then known), a packed (not plain)
+// output.
+template <typename TIn, int PREC>
+bool col_route(const PackArgs& a)
+{
+    if constexpr (!colpack_ok<PREC>() || PREC == P_PLAIN32 || PREC == P_PLAIN64) return false;
+    else return a.trans && a.L % 4 == 0 &&
+                (a.L <= 16 || std::is_same<TIn, double>::value || make_job<TIn, PREC>(a).TC % 4 == 0);
 }
 
 template <typename TIn, int PREC, int RL, int NCH>
