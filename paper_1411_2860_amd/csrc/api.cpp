@@ -805,6 +805,7 @@ struct BwdPlan {
     int64_t Gp, rg, T;
     size_t ahat, bhat, pk, dahat, dbhat, total;
     size_t p1, p2, p3, p4;
+    int cfg_a, parts_a, cfg_b, parts_b;      // tiles and k-ranges of the two contractions
 };
 
 // Workspace of the backward for projections of Gp padded groups; with
@@ -827,9 +828,13 @@ BwdPlan plan_bwd(int M, int W, int K, int L, int r, int prec, int64_t Gp, bool p
         p.ahat = off; off += align256((size_t)M * p.rg * p.T);
         p.bhat = off; off += align256((size_t)W * p.rg * p.T);
     }
-    p.pk = off; off += std::max(p.p1 + p.p2, p.p3 + p.p4);
-    p.dahat = off; off += align256((size_t)M * p.rg * p.T);
-    p.dbhat = off; off += align256((size_t)p.rg * W * p.T);
+    // all four operands at once: one pass over dR packs both of its orders
+    p.pk = off; off += p.p1 + p.p2 + p.p3 + p.p4;
+    const int KB = layout_of(prec).KB;
+    gemm_parts_plan(prec, M, p.rg, 4 * pack_geom(1, W, 4, 4, prec).Gp / KB, &p.cfg_a, &p.parts_a);
+    gemm_parts_plan(prec, p.rg, W, 4 * pack_geom(1, M, 4, 4, prec).Gp / KB, &p.cfg_b, &p.parts_b);
+    p.dahat = off; off += align256((size_t)p.parts_a * M * p.rg * p.T);
+    p.dbhat = off; off += align256((size_t)p.parts_b * p.rg * W * p.T);
     p.total = off;
     return p;
 }
@@ -866,27 +871,50 @@ int run_bwd(pj_basis b, int r, char transA, char transB, int M, int W, int K, co
         u.coef = I4; u.out = dst; u.geom = pack_geom(rows, Kc, 4, 4, prec);
         return u;
     };
-    auto gemm = [&](const void* X, int64_t P, const void* Y, int64_t Q, int64_t Kc, void* R, int64_t ldr) {
+    // P x Q product over Kc into `parts` partials of P x Q (row stride Q)
+    auto gemm = [&](const void* X, int64_t P, const void* Y, int64_t Q, int64_t Kc, void* R, int cfg, int parts) {
         GemmArgs g;
         g.X = X; g.gx = pack_geom(P, Kc, 4, 4, prec);
         g.Y = Y; g.gy = pack_geom(Q, Kc, 4, 4, prec);
         g.nkb = 4 * g.gx.Gp / layout_of(prec).KB;
-        g.P = P; g.Q = Q; g.R = R; g.ldr = ldr; g.beta = 0.0f;
-        return launch_gemm(prec, g, -1, st);
+        g.P = P; g.Q = Q; g.R = R; g.ldr = Q; g.beta = 0.0f;
+        g.nsplit = parts; g.part = parts > 1 ? R : nullptr; g.part_only = true;
+        return launch_gemm(prec, g, cfg, st);
     };
     // the unprojected operands are only re-laid out (natural contraction
-    // order); FP8 keeps the packer's identity pass for its MX scales
+    // order), dR once for both of its orders; FP8 keeps the packer's identity
+    // pass for its MX scales
     const bool fp8 = (prec == PJ_FP8 || prec == PJ_FP8X2);
-    auto pack2 = [&](const PackArgs* u) { return fp8 ? launch_pack_n(prec, u, 2, st) : launch_repack_n(prec, u, 2, st); };
     char* p1 = w + pl.pk;
+    char* p2 = p1 + pl.p1;
+    char* p3 = p2 + pl.p2;
+    char* p4 = p3 + pl.p3;
+    const PackArgs dr = unproj(dR, lddr, 0, M, W, p1), drt = unproj(dR, lddr, 1, W, M, p4);
+    const PackArgs bt = unproj(bhat, pl.rg, 1, pl.rg, W, p2), at = unproj(ahat, pl.rg, 1, pl.rg, M, p3);
+    if (fp8) {
+        const PackArgs ua[2] = {dr, bt}, ub[2] = {at, drt};
+        if (dA && launch_pack_n(prec, ua, 2, st) != 0) return PJ_ERR_HIP;
+        if (dB && launch_pack_n(prec, ub, 2, st) != 0) return PJ_ERR_HIP;
+    } else {
+        PackArgs u[3];
+        int n = 0;
+        u[n] = dA ? dr : drt;
+        if (dA && dB) {
+            u[n].out2 = drt.out;
+            u[n].geom2 = drt.geom;
+        }
+        ++n;
+        if (dA) u[n++] = bt;
+        if (dB) u[n++] = at;
+        if (launch_repack_n(prec, u, n, st) != 0) return PJ_ERR_HIP;
+    }
     if (dA) {
         // 2. dA_hat = dR B_hat: contraction over the W columns of R
-        PackArgs u[2] = {unproj(dR, lddr, 0, M, W, p1), unproj(bhat, pl.rg, 1, pl.rg, W, p1 + pl.p1)};
-        if (pack2(u) != 0) return PJ_ERR_HIP;
-        if (gemm(p1, M, p1 + pl.p1, pl.rg, W, w + pl.dahat, pl.rg) != 0) return PJ_ERR_HIP;
+        if (gemm(p1, M, p2, pl.rg, W, w + pl.dahat, pl.cfg_a, pl.parts_a) != 0) return PJ_ERR_HIP;
         // 3. dA = dA_hat spread back over each group with C
         ExpandArgs e;
         e.in = w + pl.dahat; e.ldi = pl.rg; e.in_trans = 0;
+        e.nparts = pl.parts_a; e.part = (int64_t)M * pl.rg;
         e.out = dA; e.ldo = ldda; e.out_trans = is_t(transA) ? 1 : 0;
         e.P = M; e.K = K; e.L = b->L; e.r = r; e.Gp = pl.Gp;
         e.coef = f64 ? (const void*)b->Cd : (const void*)b->Cf;
@@ -894,12 +922,11 @@ int run_bwd(pj_basis b, int r, char transA, char transB, int M, int W, int K, co
     }
     if (dB) {
         // 4. dB_hat = A_hat^T dR: contraction over the M rows of R
-        PackArgs u[2] = {unproj(ahat, pl.rg, 1, pl.rg, M, p1), unproj(dR, lddr, 1, W, M, p1 + pl.p3)};
-        if (pack2(u) != 0) return PJ_ERR_HIP;
-        if (gemm(p1, pl.rg, p1 + pl.p3, W, M, w + pl.dbhat, W) != 0) return PJ_ERR_HIP;
+        if (gemm(p3, pl.rg, p4, W, M, w + pl.dbhat, pl.cfg_b, pl.parts_b) != 0) return PJ_ERR_HIP;
         // 5. dB = dB_hat spread back over each group with D
         ExpandArgs e;
         e.in = w + pl.dbhat; e.ldi = W; e.in_trans = 1;
+        e.nparts = pl.parts_b; e.part = pl.rg * W;
         e.out = dB; e.ldo = lddb; e.out_trans = is_n(transB) ? 1 : 0;
         e.P = W; e.K = K; e.L = b->L; e.r = r; e.Gp = pl.Gp;
         e.coef = f64 ? (const void*)b->DTd : (const void*)b->DTf;

@@ -135,6 +135,9 @@ struct PackArgs {
     // (FP32, FP64 for P_F64) with the packed geometry's Gp; rows p < P only
     void* keep = nullptr;
     int64_t keep_ld = 0;
+    // repack only: the transposed operand (rows k, contraction index p) as well
+    void* out2 = nullptr;
+    PackGeom geom2 = {};
 };
 int launch_pack(int prec, const PackArgs& a, hipStream_t s);
 // Packs n (1 or 2) operands of the same precision in one launch.
@@ -143,7 +146,8 @@ int launch_pack_n(int prec, const PackArgs* a, int n, hipStream_t s);
 // index kept in its natural order, zero past K up to the geometry's padded
 // length nkb * KB; rows past P zero): the operands of the backward's
 // contractions over the rows or columns of R.  a.L, a.r and a.coef are
-// unused; a.geom gives the padded shape.  Not for the FP8 formats (-2).
+// unused; a.geom gives the padded shape.  One to three operands in one launch,
+// each optionally in both orders (out2).  Not for the FP8 formats (-2).
 int launch_repack_n(int prec, const PackArgs* a, int n, hipStream_t s);
 // Packs any number of operands in one launch, driven by a job table that is
 // copied into `table` (device memory of pack_grouped_table_bytes(n) bytes).
@@ -159,6 +163,7 @@ struct GemmArgs {
     float beta;
     int nsplit = 1;              // > 1: contiguous k-block ranges with partials in `part`
     void* part = nullptr;        // nsplit x P x Q partials (output type), caller workspace
+    bool part_only = false;      // leave the partials; their sum is the caller's
 };
 // Synthesis with the projection coefficients (the transpose of the pack's
 // projection): out(p, jL + t) = sum_{l<r} in(p, l*Gp + j) coef[t, l].
@@ -169,6 +174,7 @@ struct ExpandArgs {
     int L, r;
     int64_t Gp;
     const void* coef;                              // L x L, element (t, l)
+    int nparts = 1; int64_t part = 0;              // in = sum of nparts arrays `part` elements apart, last first
 };
 int launch_expand(int is_double, const ExpandArgs& a, hipStream_t s);
 
@@ -200,5 +206,8 @@ int gemm_config_small_tile(int prec, int cfg, int* tile_m, int* tile_n);
 int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb);
 int gemm_grouped_default_config(int prec);
 int gemm_split_count(int prec, int64_t P, int64_t Q, int64_t nkb, int cfg);
+// Tile and contiguous k-block ranges for a product whose consumer adds the
+// ranges' partials up itself (GemmArgs::part_only).
+void gemm_parts_plan(int prec, int64_t P, int64_t Q, int64_t nkb, int* cfg, int* nparts);
 
 }  // namespace pj

@@ -27,7 +27,8 @@ constexpr int kExpandMaxR = 256;
 template <typename T, bool OUT_T>
 __global__ __launch_bounds__(256) void expand_kernel(const T* __restrict__ in, int64_t ldi, int in_trans,
                                                      T* __restrict__ out, int64_t ldo, int64_t P, int64_t K, int L,
-                                                     int r, int64_t Gp, const T* __restrict__ coef, int64_t slow0)
+                                                     int r, int64_t Gp, const T* __restrict__ coef, int64_t slow0,
+                                                     int nparts, int64_t part)
 {
     __shared__ __align__(16) T cs[kExpandMaxR * kExpandChunk];      // [l][e] = coef[t0 + e, l]
     __shared__ T st[OUT_T ? 1 : 256 * (kExpandChunk + 1)];          // row-major output: runs re-dealt to lanes
@@ -58,7 +59,9 @@ __global__ __launch_bounds__(256) void expand_kernel(const T* __restrict__ in, i
         if (t0 < tlim)
             for (int l = 0; l < r; ++l) {
                 const int64_t kk = (int64_t)l * Gp + j;
-                const T v = in_trans ? in[kk * ldi + p] : in[p * ldi + kk];
+                const T* src = in + (in_trans ? kk * ldi + p : p * ldi + kk);
+                T v = src[(nparts - 1) * part];
+                for (int q = nparts - 2; q >= 0; --q) v += src[q * part];
                 const T* c = cs + l * kExpandChunk;
 #pragma unroll
                 for (int e = 0; e < kExpandChunk; ++e) acc[e] += v * c[e];
@@ -88,10 +91,147 @@ __global__ __launch_bounds__(256) void expand_kernel(const T* __restrict__ in, i
     }
 }
 
+// in(p, kk) of RC projections l = 0 .. RC - 1 (zero from r up), the partials
+// added last first; all loads of a partial in flight together.
+template <int RC>
+__device__ __forceinline__ void load_projected(const float* __restrict__ src, int64_t step, int r, int nparts,
+                                               int64_t part, float (&v)[RC])
+{
+#pragma unroll
+    for (int l = 0; l < RC; ++l) v[l] = src[(nparts - 1) * part + (l < r ? l : 0) * step];
+    for (int q = nparts - 2; q >= 0; --q) {
+        float u[RC];
+#pragma unroll
+        for (int l = 0; l < RC; ++l) u[l] = src[q * part + (l < r ? l : 0) * step];
+#pragma unroll
+        for (int l = 0; l < RC; ++l) v[l] += u[l];
+    }
+#pragma unroll
+    for (int l = 0; l < RC; ++l) v[l] = l < r ? v[l] : 0.0f;
+}
+
+// Few projections, FP32.  Row-major output and input, L a multiple of 4: a
+// thread owns 4 consecutive indices t of a group (the same in every group it
+// visits, so its 4 x RC coefficients stay in registers), L / 4 threads a group,
+// and a wave stores 1 KB of one row.  The workgroup stages the projected values
+// of kExRows rows and kExGroups groups in LDS, [row][l][group].  Bound by HBM
+// (the output): 4096 x 4096, L = 64, r = 8 (67 MB written): 33.6 us with 64-byte
+// runs through LDS, 28 us from four partials of the projected gradient (33 us with its
+// loads one after another).
+constexpr int kExRows = 4, kExGroups = 64;
+
+template <int RC>
+__global__ __launch_bounds__(256) void expand_rows_kernel(const float* __restrict__ in, int64_t ldi,
+                                                          float* __restrict__ out, int64_t ldo, int64_t P, int64_t K,
+                                                          int L, int r, int64_t Gp, const float* __restrict__ coef,
+                                                          int nparts, int64_t part)
+{
+    static_assert(kExRows * kExGroups == 256, "one thread a row and group");
+    __shared__ float xs[kExRows][RC][kExGroups];
+    const int64_t G = (K + L - 1) / L;
+    const int64_t p0 = (int64_t)blockIdx.x * kExRows, j0 = (int64_t)blockIdx.y * kExGroups;
+    const int ng = (int)(G - j0 < kExGroups ? G - j0 : kExGroups);
+    const int tpg = L / 4, gpp = 256 / tpg;              // threads a group, groups a pass
+    const int t = 4 * (threadIdx.x % tpg), gt = threadIdx.x / tpg;
+    {
+        const int j = threadIdx.x % kExGroups, row = threadIdx.x / kExGroups;
+        float v[RC];
+        const int64_t p = p0 + row < P ? p0 + row : P - 1;
+        load_projected<RC>(in + p * ldi + j0 + (j < ng ? j : 0), Gp, r, nparts, part, v);
+#pragma unroll
+        for (int l = 0; l < RC; ++l) xs[row][l][j] = v[l];
+    }
+    float c[RC][4];
+#pragma unroll
+    for (int l = 0; l < RC; ++l)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[l][e] = coef[(t + e) * L + (l < r ? l : 0)];
+    __syncthreads();
+    if (gt >= gpp) return;                               // 256 is not a multiple of L / 4
+    for (int row = 0; row < kExRows && p0 + row < P; ++row)
+        for (int g = gt; g < ng; g += gpp) {
+            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int l = 0; l < RC; ++l) {
+                const float x = xs[row][l][g];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += x * c[l][e];
+            }
+            const int64_t k = (j0 + g) * L + t;
+            float* dst = out + (p0 + row) * ldo + k;
+            if (k + 3 < K) {
+                *reinterpret_cast<f32x4*>(dst) = acc;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k + e < K) dst[e] = acc[e];
+            }
+        }
+}
+
+// Transposed output and input (p contiguous in both): one thread per (p, group
+// j) keeps the group's RC values in registers for all L outputs; coefficients
+// from LDS.  4096 x 4096, L = 64, r = 8: 22 us reading them again for every 16
+// outputs (41 us from four partials), 18 us from four partials.
+template <int RC>
+__global__ __launch_bounds__(256) void expand_cols_kernel(const float* __restrict__ in, int64_t ldi,
+                                                          float* __restrict__ out, int64_t ldo, int64_t P, int64_t K,
+                                                          int L, int r, int64_t Gp, const float* __restrict__ coef,
+                                                          int nparts, int64_t part)
+{
+    __shared__ __align__(16) float cs[256 * RC];         // [t][l]
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t j = blockIdx.y;
+    float v[RC];
+    load_projected<RC>(in + j * ldi + (p < P ? p : P - 1), Gp * ldi, r, nparts, part, v);
+    for (int x = threadIdx.x; x < L * RC; x += 256) cs[x] = coef[(x / RC) * L + (x % RC < r ? x % RC : 0)];
+    __syncthreads();
+    if (p >= P) return;
+    const int n = (int)(K - j * L < L ? K - j * L : L);  // the last group may be partial
+    float* dst = out + j * L * ldo + p;
+#pragma unroll 4
+    for (int t = 0; t < n; ++t) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int l = 0; l < RC; ++l) acc += v[l] * cs[t * RC + l];
+        dst[t * ldo] = acc;
+    }
+}
+
+// The kernels above where they apply: 1 launched, 0 not applicable, -1 failed.
+int launch_few(const ExpandArgs& a, hipStream_t s)
+{
+    if (a.r > 16 || a.L > 256 || a.in_trans != a.out_trans) return 0;
+    const int64_t G = cdiv(a.K, a.L);
+#define PJ_EXF(KERN_, RC_, GX_, GY_)                                                                              \
+    hipLaunchKernelGGL(KERN_<RC_>, dim3((unsigned)(GX_), (unsigned)(GY_)), dim3(256), 0, s, (const float*)a.in, a.ldi, \
+                       (float*)a.out, a.ldo, a.P, a.K, a.L, a.r, a.Gp, (const float*)a.coef, a.nparts, a.part)
+    if (a.out_trans) {
+        const int64_t gx = cdiv(a.P, 256);
+        if (gx > 0x7fffffff || G > 65535) return 0;
+        if (a.r <= 4) PJ_EXF(expand_cols_kernel, 4, gx, G);
+        else if (a.r <= 8) PJ_EXF(expand_cols_kernel, 8, gx, G);
+        else PJ_EXF(expand_cols_kernel, 16, gx, G);
+    } else {
+        if (a.L % 4 != 0 || a.ldo % 4 != 0 || (uintptr_t)a.out % 16 != 0) return 0;
+        const int64_t gx = cdiv(a.P, kExRows), gy = cdiv(G, kExGroups);
+        if (gx > 0x7fffffff || gy > 65535) return 0;
+        if (a.r <= 4) PJ_EXF(expand_rows_kernel, 4, gx, gy);
+        else if (a.r <= 8) PJ_EXF(expand_rows_kernel, 8, gx, gy);
+        else PJ_EXF(expand_rows_kernel, 16, gx, gy);
+    }
+#undef PJ_EXF
+    return hipGetLastError() == hipSuccess ? 1 : -1;
+}
+
 template <typename T>
 int launch_t(const ExpandArgs& a, hipStream_t s)
 {
     if (a.r < 1 || a.r > kExpandMaxR || a.L < 1) return -2;
+    if constexpr (sizeof(T) == 4) {
+        const int e = launch_few(a, s);
+        if (e != 0) return e < 0 ? e : 0;
+    }
     const int64_t G = cdiv(a.K, a.L);
     const int64_t fast = a.out_trans ? a.P : a.P * G;
     const int64_t slow = a.out_trans ? G : 1;
@@ -102,11 +242,11 @@ int launch_t(const ExpandArgs& a, hipStream_t s)
         if (a.out_trans)
             hipLaunchKernelGGL((expand_kernel<T, true>), dim3((unsigned)cdiv(fast, 256), (unsigned)ny), dim3(256), 0,
                                s, (const T*)a.in, a.ldi, a.in_trans, (T*)a.out, a.ldo, a.P, a.K, a.L, a.r, a.Gp,
-                               (const T*)a.coef, y0);
+                               (const T*)a.coef, y0, a.nparts, a.part);
         else
             hipLaunchKernelGGL((expand_kernel<T, false>), dim3((unsigned)cdiv(fast, 256), (unsigned)ny), dim3(256), 0,
                                s, (const T*)a.in, a.ldi, a.in_trans, (T*)a.out, a.ldo, a.P, a.K, a.L, a.r, a.Gp,
-                               (const T*)a.coef, y0);
+                               (const T*)a.coef, y0, a.nparts, a.part);
         if (hipGetLastError() != hipSuccess) return -1;
     }
     return 0;

@@ -1283,7 +1283,7 @@ int launch_gemm_t(const GemmArgs& a, hipStream_t s)
                        (const char*)a.Y, a.gy.nrb, a.gy.nkb, a.gy.plane_bytes + a.gy.scale_plane, a.gy.plane_bytes,
                        a.nkb, a.P, a.Q, (OT*)a.R, a.ldr, a.beta, tiles_m, ntiles, ns, (OT*)a.part);
     if (hipGetLastError() != hipSuccess) return -1;
-    if (ns > 1) {
+    if (ns > 1 && !a.part_only) {
         hipLaunchKernelGGL(gemm_split_sum_kernel<OT>, dim3((unsigned)cdiv(a.P * a.Q, 256)), dim3(256), 0, s,
                            (const OT*)a.part, ns, a.P, a.Q, (OT*)a.R, a.ldr, a.beta);
         if (hipGetLastError() != hipSuccess) return -1;
@@ -1475,6 +1475,25 @@ int gemm_split_count(int prec, int64_t P, int64_t Q, int64_t nkb, int cfg)
     int64_t ns = std::min<int64_t>(cdiv(256, tiles), nkb / 32);
     ns = std::min<int64_t>(ns, 64);
     return (int)std::max<int64_t>(ns, 1);
+}
+
+// The backward's products have one short side (r * ceil(K / L)) and a long
+// contraction, so their tiles leave most CUs idle: 256 x 128 tiles over ranges of
+// at least 32 k-blocks where those give at least half the CUs a workgroup, at
+// most 8 ranges (each is a pass over a P x Q array for the consumer).  4096 x 512
+// over 4096, BF16, as the 64 x 64 direct tiles of gemm_default_config: 44.5 us,
+// as four ranges of 64 tiles: 28.5 us, their sum inside the synthesis.
+void gemm_parts_plan(int prec, int64_t P, int64_t Q, int64_t nkb, int* cfg, int* nparts)
+{
+    *cfg = gemm_default_config(prec, P, Q, nkb);
+    *nparts = 1;
+    if (prec == P_F64 || prec == P_FP8 || prec == P_FP8X2) return;
+    const int64_t tiles = cdiv(P, 256) * cdiv(Q, 128);
+    if (tiles > 128) return;
+    const int64_t n = std::min<int64_t>(std::min<int64_t>(256 / tiles, nkb / (prec == P_F32 ? 64 : 32)), 8);
+    if (n < 2 || tiles * n < 128) return;
+    *cfg = prec == P_F32 ? 20 : 16;
+    *nparts = (int)n;
 }
 
 int launch_gemm(int prec, const GemmArgs& a, int cfg, hipStream_t s)

@@ -1374,8 +1374,13 @@ int launch_grouped_rows(const PackArgs* a, int n, void* table, hipStream_t s)
 // ---- unprojected operands ----------------------------------------------------
 // A workgroup copies a kRpRows x kRpK block of the source (rows p, natural
 // contraction index k) into LDS with coalesced loads along whichever index
-// is contiguous in memory, then writes the block's packed tiles, one 16-byte
-// lane vector per lane slot, converted as the format's packer does.
+// is contiguous in memory, all of a thread's loads in flight together, then
+// writes the block's packed tiles, one 16-byte lane vector per lane slot,
+// converted as the format's packer does.  A second output takes the transposed
+// operand (rows k, contraction index p) from the same block: the backward
+// contracts dR over its columns and over its rows, and reads it once.  Bound
+// by HBM: dR of 4096 x 4096 in BF16 in both orders with two small operands
+// (159 MB) 30 us, 68 us in two launches of four loads in flight.
 constexpr int kRpRows = 64, kRpK = 64;
 
 template <typename TIn>
@@ -1384,6 +1389,8 @@ struct RepackJob {
     int64_t P, K;
     char* out;
     int64_t nrb, nkb, plane_stride;
+    char* out2;                   // transposed operand (nullptr: none)
+    int64_t nrb2, nkb2, plane_stride2;
     int64_t ntk, nblk;            // k blocks of the workgroup grid, workgroups
 };
 
@@ -1392,45 +1399,60 @@ __device__ __forceinline__ void repack_block(const RepackJob<TIn>& J, int64_t b)
 {
     constexpr Layout ly = layout_of(PREC);
     constexpr int RB = ly.RB, KB = ly.KB, E = ly.E;
+    constexpr int NQ = kRpRows / (kPackThreads / 64);
     __shared__ TIn sm[kRpRows][kRpK + 1];
     const int64_t p0 = (b / J.ntk) * kRpRows, k0 = (b % J.ntk) * kRpK;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // 64 consecutive elements of the contiguous index per wave instruction
-#pragma unroll 4
-    for (int q = wave; q < kRpRows; q += kPackThreads / 64) {
-        int rr, kk;
-        if (J.trans) { kk = q; rr = lane; }      // source row k0 + q, elements p0 .. p0 + 63
-        else { rr = q; kk = lane; }              // source row p0 + q, elements k0 .. k0 + 63
-        const int64_t p = p0 + rr, k = k0 + kk;
-        TIn v = (TIn)0;
-        if (p < J.P && k < J.K) v = J.trans ? J.X[k * J.ld + p] : J.X[p * J.ld + k];
-        sm[rr][kk] = v;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // 64 consecutive elements of the contiguous index per wave instruction:
+    // source row k0 + q, elements p0 .. p0 + 63 (trans), or row p0 + q, elements
+    // k0 .. k0 + 63; places outside the operand read its first element
+    const int64_t row0 = J.trans ? k0 : p0, col = (J.trans ? p0 : k0) + lane;
+    const int64_t nrow = J.trans ? J.K : J.P, ncol = J.trans ? J.P : J.K;
+    TIn v[NQ];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const int64_t row = row0 + wave + i * (kPackThreads / 64);
+        const bool in = row < nrow && col < ncol;
+        const TIn x = J.X[in ? row * J.ld + col : 0];
+        v[i] = in ? x : (TIn)0;
+    }
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const int q = wave + i * (kPackThreads / 64);
+        if (J.trans) sm[lane][q] = v[i];
+        else sm[q][lane] = v[i];
     }
     __syncthreads();
     constexpr int NTB = (kRpRows / RB) * (kRpK / KB);     // tiles of the block
+    static_assert(kRpRows == kRpK, "both orders have the same tiles");
+    auto write = [&](char* out, int64_t r0, int64_t c0, int64_t nrb, int64_t nkb, int64_t plane, auto at) {
 #pragma unroll
-    for (int s0 = 0; s0 < NTB * 64; s0 += kPackThreads) {
-        const int s = s0 + tid;
-        const int q = s / 64, ln = s % 64;
-        const int rbl = q / (kRpK / KB), kbl = q % (kRpK / KB);
-        const int64_t rb = p0 / RB + rbl, kb = k0 / KB + kbl;
-        if (rb < J.nrb && kb < J.nkb) {
-            const int g = ln / RB, rib = ln % RB;
-            TIn v[E];
+        for (int s0 = 0; s0 < NTB * 64; s0 += kPackThreads) {
+            const int s = s0 + tid;
+            const int q = s / 64, ln = s % 64;
+            const int rbl = q / (kRpK / KB), kbl = q % (kRpK / KB);
+            const int64_t rb = r0 / RB + rbl, kb = c0 / KB + kbl;
+            if (rb < nrb && kb < nkb) {
+                const int g = ln / RB, rib = ln % RB;
+                TIn w[E];
 #pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = sm[rbl * RB + rib][kbl * KB + g * E + e];
-            store_lane<PREC, E, TIn>(J.out, ((rb * J.nkb + kb) * 64 + ln) * (int64_t)ly.LB, J.plane_stride, 0, v);
+                for (int e = 0; e < E; ++e) w[e] = at(rbl * RB + rib, kbl * KB + g * E + e);
+                store_lane<PREC, E, TIn>(out, ((rb * nkb + kb) * 64 + ln) * (int64_t)ly.LB, plane, 0, w);
+            }
         }
-    }
-    (void)lane;
+    };
+    write(J.out, p0, k0, J.nrb, J.nkb, J.plane_stride, [&](int r, int c) { return sm[r][c]; });
+    if (J.out2) write(J.out2, k0, p0, J.nrb2, J.nkb2, J.plane_stride2, [&](int r, int c) { return sm[c][r]; });
 }
 
 template <typename TIn, int PREC>
-__global__ __launch_bounds__(kPackThreads) void repack_kernel(RepackJob<TIn> ja, RepackJob<TIn> jb)
+__global__ __launch_bounds__(kPackThreads) void repack_kernel(RepackJob<TIn> ja, RepackJob<TIn> jb, RepackJob<TIn> jc)
 {
     const int64_t b = blockIdx.x;
     if (b < ja.nblk) repack_block<TIn, PREC>(ja, b);
-    else repack_block<TIn, PREC>(jb, b - ja.nblk);
+    else if (b < ja.nblk + jb.nblk) repack_block<TIn, PREC>(jb, b - ja.nblk);
+    else repack_block<TIn, PREC>(jc, b - ja.nblk - jb.nblk);
 }
 
 template <typename TIn, int PREC>
@@ -1447,21 +1469,33 @@ RepackJob<TIn> make_repack(const PackArgs& a)
     j.nrb = a.geom.nrb;
     j.nkb = a.geom.nkb;
     j.plane_stride = a.geom.plane_bytes + a.geom.scale_plane;
-    j.ntk = cdiv(j.nkb * ly.KB, kRpK);
-    j.nblk = cdiv(j.nrb * ly.RB, kRpRows) * j.ntk;
+    j.out2 = (char*)a.out2;
+    j.nrb2 = a.geom2.nrb;
+    j.nkb2 = a.geom2.nkb;
+    j.plane_stride2 = a.geom2.plane_bytes + a.geom2.scale_plane;
+    int64_t rows = j.nrb * ly.RB, ks = j.nkb * ly.KB;      // padded extents of the orders written
+    if (j.out2) {
+        rows = std::max(rows, j.nkb2 * ly.KB);
+        ks = std::max(ks, j.nrb2 * ly.RB);
+    }
+    j.ntk = cdiv(ks, kRpK);
+    j.nblk = cdiv(rows, kRpRows) * j.ntk;
     return j;
 }
 
 template <typename TIn, int PREC>
 int launch_repack_t(const PackArgs* a, int n, hipStream_t s)
 {
-    const RepackJob<TIn> ja = make_repack<TIn, PREC>(a[0]);
-    RepackJob<TIn> jb = n > 1 ? make_repack<TIn, PREC>(a[1]) : ja;
-    if (n < 2) jb.nblk = 0;
-    const int64_t grid = ja.nblk + jb.nblk;
+    RepackJob<TIn> j[3];
+    int64_t grid = 0;
+    for (int i = 0; i < 3; ++i) {
+        j[i] = make_repack<TIn, PREC>(a[i < n ? i : 0]);
+        if (i >= n) j[i].nblk = 0;
+        grid += j[i].nblk;
+    }
     if (grid > 0x7fffffff) return -2;
     if (grid == 0) return 0;
-    hipLaunchKernelGGL((repack_kernel<TIn, PREC>), dim3((unsigned)grid), dim3(kPackThreads), 0, s, ja, jb);
+    hipLaunchKernelGGL((repack_kernel<TIn, PREC>), dim3((unsigned)grid), dim3(kPackThreads), 0, s, j[0], j[1], j[2]);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
