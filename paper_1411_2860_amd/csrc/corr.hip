@@ -21,8 +21,8 @@
 //     grouped as (s C)(D k) or s (C D k); the second needs no projection of
 //     the signal and L instead of r channels.
 //
-// A workgroup (4 waves) owns 512 consecutive rows; lane j of a wave owns rows
-// 8j .. 8j + 7 and slides a 16-value window of X along the taps, so every
+// A workgroup (4 waves) owns 512 consecutive rows (fewer on more waves for
+// short signals); lane j of a wave owns rows 8j .. 8j + 7 and slides a 16-value window of X along the taps, so every
 // pair of 16-byte LDS reads feeds 64 FMAs per phase.  The waves share the
 // channels (or, with fewer than 4 channels, the taps) of each staged tile and
 // their sums are added in a fixed order at the end.
@@ -37,24 +37,42 @@ namespace {
 constexpr int kOPT = 8;            // consecutive output rows per lane
 constexpr int kTA = 64 * kOPT;     // output rows per workgroup
 constexpr int kCT = 256;           // threads per workgroup
+constexpr int kNW = kCT / 64;      // (the small kernel also has cuts of its own)
 constexpr int kBlockTC = 128;      // taps per staged tile, block rate
 constexpr int kBlockCH = 8;        // channels per staged tile, block rate
 
 // Accumulates taps [cb, ce) (multiples of 8) of one channel into the lane's
-// kOPT rows for NPH phases.  xw[i] = X(ch, row0 + i) of the staged window
-// (the lane's rows start at i = 8 lane), hw[p * hps + c] = H(p, ch, c0 + c).
-template <int NPH>
+// OPT rows for NPH phases.  xw[i] = X(ch, row0 + i) of the staged window
+// (the lane's rows start at i = OPT lane), hw[p * hps + c] = H(p, ch, c0 + c).
+template <int NPH, int OPT>
 __device__ __forceinline__ void corr_taps(const float* __restrict__ xw, const float* __restrict__ hw, int hps, int cb,
-                                          int ce, int lane, float (&acc)[NPH][kOPT])
+                                          int ce, int lane, float (&acc)[NPH][OPT])
 {
-    const float* xl = xw + kOPT * lane;
-    f32x4 w0 = *reinterpret_cast<const f32x4*>(xl + cb);
-    f32x4 w1 = *reinterpret_cast<const f32x4*>(xl + cb + 4);
+    const float* xl = xw + OPT * lane;
+    float w[OPT + 8];                  // the window of 8 taps; its first OPT values carry over
+    if constexpr (OPT % 4 == 0) {
+#pragma unroll
+        for (int i = 0; i < OPT; i += 4) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(xl + cb + i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[i + e] = v[e];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < OPT; ++i) w[i] = xl[cb + i];
+    }
     for (int c = cb; c < ce; c += 8) {
-        const f32x4 w2 = *reinterpret_cast<const f32x4*>(xl + c + 8);
-        const f32x4 w3 = *reinterpret_cast<const f32x4*>(xl + c + 12);
-        const float w[16] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3],
-                             w2[0], w2[1], w2[2], w2[3], w3[0], w3[1], w3[2], w3[3]};
+        if constexpr (OPT % 4 == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 4) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(xl + c + OPT + i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[OPT + i + e] = v[e];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w[OPT + i] = xl[c + OPT + i];
+        }
 #pragma unroll
         for (int p = 0; p < NPH; ++p) {
             const f32x4 h0 = *reinterpret_cast<const f32x4*>(hw + p * hps + c);
@@ -63,58 +81,49 @@ __device__ __forceinline__ void corr_taps(const float* __restrict__ xw, const fl
 #pragma unroll
             for (int e = 0; e < 8; ++e)
 #pragma unroll
-                for (int o = 0; o < kOPT; ++o) acc[p][o] = fmaf(w[o + e], h[e], acc[p][o]);
+                for (int o = 0; o < OPT; ++o) acc[p][o] = fmaf(w[o + e], h[e], acc[p][o]);
         }
-        w0 = w2;
-        w1 = w3;
+#pragma unroll
+        for (int i = 0; i < OPT; ++i) w[i] = w[8 + i];
     }
 }
 
-// The share of a staged tile (nch channels, taps [0, ntc)) that wave w
-// contracts: with at least 4 channels the waves take channels w, w + 4, ...
-// from the highest down (small high-order terms first), all taps; otherwise
-// every wave takes every channel and a quarter of the taps.
+// The share of a staged tile (nch channels, taps [0, ntc)) that wave w of NW
+// contracts: with at least 4 channels the waves take channels w % 4, w % 4 + 4, ...
+// from the highest down (small high-order terms first) and range w / 4 of NW / 4
+// ranges of the taps; otherwise every wave takes every channel and one of NW
+// ranges of the taps.
 struct Share {
     bool by_channel;
-    int cb, ce;        // tap range (tap split)
+    int cb, ce;        // tap range
 };
+template <int NW>
 __device__ __forceinline__ Share wave_share(int nch, int ntc, int w)
 {
     Share s;
     s.by_channel = nch >= 4;
-    if (s.by_channel) {
-        s.cb = 0;
-        s.ce = ntc;
-    } else {
-        const int q = ((ntc + 31) / 32) * 8;      // quarter, multiple of 8
-        s.cb = min(w * q, ntc);
-        s.ce = min((w + 1) * q, ntc);
-    }
+    const int ranges = s.by_channel ? NW / 4 : NW, i = s.by_channel ? w / 4 : w;
+    const int q = ((ntc + 8 * ranges - 1) / (8 * ranges)) * 8;      // multiple of 8
+    s.cb = min(i * q, ntc);
+    s.ce = min((i + 1) * q, ntc);
     return s;
 }
 
 // Contracts the staged tile: X window rows of length rl per channel (LDS xs),
-// taps hs[(p * nch + ch) * tcs + c] (tcs taps per row); optional halo row kTA
+// taps hs[(p * nch + ch) * tcs + c] (tcs taps per row); optional halo row 64 OPT
 // for phase 0 (block rate), accumulated over the same share.
-template <int NPH, bool HALO>
+template <int NPH, int OPT, int NW, bool HALO>
 __device__ __forceinline__ void corr_tile(const float* __restrict__ xs, int rl, const float* __restrict__ hs, int tcs,
-                                          int nch, int ntc, int w, int lane, float (&acc)[NPH][kOPT], float& halo)
+                                          int nch, int ntc, int w, int lane, float (&acc)[NPH][OPT], float& halo)
 {
-    const Share sh = wave_share(nch, ntc, w);
+    const Share sh = wave_share<NW>(nch, ntc, w);
     const int hps = nch * tcs;
-    if (sh.by_channel) {
-        for (int ch = nch - 1 - w; ch >= 0; ch -= 4) {
-            corr_taps<NPH>(xs + ch * rl, hs + ch * tcs, hps, 0, ntc, lane, acc);
-            if (HALO)
-                for (int c = lane; c < ntc; c += 64) halo = fmaf(xs[ch * rl + kTA + c], hs[ch * tcs + c], halo);
-        }
-    } else {
-        for (int ch = nch - 1; ch >= 0; --ch) {
-            if (sh.cb < sh.ce) corr_taps<NPH>(xs + ch * rl, hs + ch * tcs, hps, sh.cb, sh.ce, lane, acc);
-            if (HALO)
-                for (int c = sh.cb + lane; c < sh.ce; c += 64)
-                    halo = fmaf(xs[ch * rl + kTA + c], hs[ch * tcs + c], halo);
-        }
+    if (sh.cb >= sh.ce) return;
+    for (int ch = nch - 1 - (sh.by_channel ? w % 4 : 0); ch >= 0; ch -= sh.by_channel ? 4 : 1) {
+        corr_taps<NPH, OPT>(xs + ch * rl, hs + ch * tcs, hps, sh.cb, sh.ce, lane, acc);
+        if (HALO)
+            for (int c = sh.cb + lane; c < sh.ce; c += 64)
+                halo = fmaf(xs[ch * rl + 64 * OPT + c], hs[ch * tcs + c], halo);
     }
 }
 
@@ -125,72 +134,82 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// dst(x) = src(x) for x < n over the workgroup's threads, with 8 loads of a
+// dst(x) = src(x) for x < n over the workgroup's NT threads, with 8 loads of a
 // thread in flight before its first store (a staging loop that stores each
 // value before loading the next waits out the memory latency every time).
-template <typename Ld, typename St>
+template <int NT, typename Ld, typename St>
 __device__ __forceinline__ void stage_copy(int n, Ld ld, St st)
 {
-    for (int base = threadIdx.x; base < n; base += 8 * kCT) {
+    for (int base = threadIdx.x; base < n; base += 8 * NT) {
         float v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int x = base + j * kCT;
+            const int x = base + j * NT;
             v[j] = x < n ? ld(x) : 0.0f;
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int x = base + j * kCT;
+            const int x = base + j * NT;
             if (x < n) st(x, v[j]);
         }
     }
 }
 
-// Epilogue shared by both kernels: the four waves' row sums are added in a
-// fixed order (wave 3 first), then written as
-//   mode 0: y[a0 L + f] = Y for f < kTA NPH (full rate, f = row NPH + p);
-//   mode 1: block rate, y[m] for m in [a0 L, (a0 + kTA) L) interpolated
-//           between the computed samples (the halo supplies row kTA);
+// Epilogue shared by both kernels: the waves' row sums are added in a
+// fixed order (highest wave first), then written as
+//   mode 0: y[a0 L + f] = Y for f < TA NPH (full rate, f = row NPH + p);
+//   mode 1: block rate, y[m] for m in [a0 L, (a0 + TA) L) interpolated
+//           between the computed samples (the halo supplies row TA);
 //   mode 2: partial sums part[a] of this channel range (rows a < nd).
-template <int NPH>
-__device__ __forceinline__ void corr_finish(float* red, const float (&acc)[NPH][kOPT], float halo, int mode,
+template <int NPH, int OPT, int NW>
+__device__ __forceinline__ void corr_finish(float* red, const float (&acc)[NPH][OPT], float halo, int mode,
                                             int64_t a0, int64_t nd, int L, int64_t nout, float* __restrict__ y,
                                             float* __restrict__ part)
 {
+    constexpr int TA = 64 * OPT, NT = 64 * NW;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    constexpr int NF = kTA * NPH;
+    constexpr int NF = TA * NPH;
     __syncthreads();      // the staged tiles may alias `red`
 #pragma unroll
-    for (int o = 0; o < kOPT; ++o)
+    for (int o = 0; o < OPT; ++o)
 #pragma unroll
-        for (int p = 0; p < NPH; ++p) red[w * NF + (kOPT * lane + o) * NPH + p] = acc[p][o];
+        for (int p = 0; p < NPH; ++p) red[w * NF + (OPT * lane + o) * NPH + p] = acc[p][o];
     float hs = 0.0f;
     if (mode == 1) hs = wave_sum(halo);
-    if (mode == 1 && lane == 0) red[4 * NF + w] = hs;
+    if (mode == 1 && lane == 0) red[NW * NF + w] = hs;
     __syncthreads();
+    auto sum = [&](int f) {
+        float v = red[(NW - 1) * NF + f];
+#pragma unroll
+        for (int i = NW - 2; i >= 0; --i) v += red[i * NF + f];
+        return v;
+    };
     if (mode == 0) {
-        for (int f = tid; f < NF; f += kCT) {
+        for (int f = tid; f < NF; f += NT) {
             const int64_t m = a0 * L + f;
-            if (m < nout) y[m] = ((red[3 * NF + f] + red[2 * NF + f]) + red[NF + f]) + red[f];
+            if (m < nout) y[m] = sum(f);
         }
         return;
     }
     if (mode == 2) {
-        for (int f = tid; f < kTA; f += kCT) {
+        for (int f = tid; f < TA; f += NT) {
             const int64_t a = a0 + f;
-            if (a < nd) part[a] = ((red[3 * NF + f] + red[2 * NF + f]) + red[NF + f]) + red[f];
+            if (a < nd) part[a] = sum(f);
         }
         return;
     }
-    // block rate: yd[row] for rows 0 .. kTA (the last from the halo), kept in
-    // the wave-0 slice of red after the other slices are added in
-    float* yd = red + 5 * NF;
-    for (int f = tid; f < kTA; f += kCT) yd[f] = ((red[3 * NF + f] + red[2 * NF + f]) + red[NF + f]) + red[f];
-    if (tid == 0) yd[kTA] = ((red[4 * NF + 3] + red[4 * NF + 2]) + red[4 * NF + 1]) + red[4 * NF];
+    // block rate: yd[row] for rows 0 .. TA (the last from the halo)
+    float* yd = red + NW * NF + NW;
+    for (int f = tid; f < TA; f += NT) yd[f] = sum(f);
+    if (tid == 0) {
+        float v = red[NW * NF + NW - 1];
+        for (int i = NW - 2; i >= 0; --i) v += red[NW * NF + i];
+        yd[TA] = v;
+    }
     __syncthreads();
     const int64_t mlo = a0 * L;
-    const int nq = (int)((a0 + kTA) * L < nout ? kTA * L : nout - mlo);   // at most kTA L <= 4096
-    for (int q = tid; q < nq; q += kCT) {
+    const int nq = (int)((a0 + TA) * L < nout ? TA * L : nout - mlo);   // at most TA L <= 4096
+    for (int q = tid; q < nq; q += NT) {
         const int row = q / L, f = q - row * L;
         float v = yd[row];
         if (f != 0 && a0 + row + 1 < nd) v += ((float)f / (float)L) * (yd[row + 1] - v);
@@ -198,11 +217,14 @@ __device__ __forceinline__ void corr_finish(float* red, const float (&acc)[NPH][
     }
 }
 
-// LDS floats of the epilogue: 4 wave slices, the halo sums and the yd rows.
-template <int NPH>
-constexpr int finish_floats() { return 5 * kTA * NPH + kTA + 8; }
+// LDS floats of the epilogue: the wave slices, the halo sums and the yd rows.
+template <int NPH, int OPT, int NW>
+constexpr int finish_floats() { return NW * 64 * OPT * NPH + NW + 64 * OPT + 8; }
 
 // ---- blocks of at most 8 samples: everything in one launch ---------------
+// A workgroup of NW waves owns 64 OPT rows.  With few rows the whole call is one
+// round of workgroups, as long as the sums of one of them: those are cut to 128
+// or 64 rows, their taps dealt to 8 or 16 waves.
 constexpr int kSmallMaxL = 8;
 constexpr int kSmallBudget = 16384;      // LDS floats for a staged tile (64 KiB)
 
@@ -211,66 +233,67 @@ constexpr int kSmallBudget = 16384;      // LDS floats for a staged tile (64 KiB
 // (the kernel segment is padded to a multiple of 4 floats so that the taps
 // after it stay 16-byte aligned for any L)
 __host__ __device__ constexpr int small_kseg_floats(int L, int tc) { return (tc * L + 2 * L + 3) / 4 * 4; }
-__host__ __device__ constexpr int small_stage_floats(int L, int r, int nph, int tc)
+__host__ __device__ constexpr int small_stage_floats(int ta, int L, int r, int nph, int tc)
 {
-    return (kTA + tc + 4) * L + r * (kTA + tc + 4) + small_kseg_floats(L, tc) + nph * r * tc;
+    return (ta + tc + 4) * L + r * (ta + tc + 4) + small_kseg_floats(L, tc) + nph * r * tc;
 }
 
-// dynamic LDS: max(small_stage_floats(L, r, NPH, tc), finish_floats<NPH>())
-template <int NPH>
-__global__ __launch_bounds__(kCT) void corr_small_kernel(CorrSmallArgs p, int tcmax)
+// dynamic LDS: max(small_stage_floats(64 OPT, L, r, NPH, tc), finish_floats<NPH, OPT, NW>())
+template <int NPH, int OPT, int NW>
+__global__ __launch_bounds__(64 * NW) void corr_small_kernel(CorrSmallArgs p, int tcmax)
 {
     extern __shared__ __align__(16) float lds[];
+    constexpr int TA = 64 * OPT, NT = 64 * NW;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = p.L, r = p.r;
-    const int rlm = kTA + tcmax + 4;                    // row stride of the staged windows
+    const int rlm = TA + tcmax + 4;                     // row stride of the staged windows
     float* ss = lds;                                    // [rl * L]   raw signal of the window
     float* xs = ss + rlm * L;                           // [r][rlm]   projected channels
     float* ks = xs + r * rlm;                           // kernel segment
     float* hs = ks + small_kseg_floats(L, tcmax);       // [NPH][r][tcmax] taps
-    const int64_t a0 = (int64_t)blockIdx.x * kTA;
+    const int64_t a0 = (int64_t)blockIdx.x * TA;
     const int64_t ntp = (p.ntap + 7) / 8 * 8;
     const bool halo_on = p.block != 0;
 
-    float acc[NPH][kOPT];
+    float acc[NPH][OPT];
 #pragma unroll
     for (int q = 0; q < NPH; ++q)
 #pragma unroll
-        for (int o = 0; o < kOPT; ++o) acc[q][o] = 0.0f;
+        for (int o = 0; o < OPT; ++o) acc[q][o] = 0.0f;
     float halo = 0.0f;
 
     for (int64_t c0 = 0; c0 < ntp; c0 += tcmax) {
         const int tc = (int)(ntp - c0 < tcmax ? ntp - c0 : tcmax);
         const int64_t i0 = a0 + c0;                     // first staged row
-        const int rl = kTA + tc + 4;
+        const int rl = TA + tc + 4;
         __syncthreads();                                // previous tile consumed
         // raw signal samples of rows i0 .. i0 + rl (zero past W, or periodic)
         const int64_t n0 = i0 * L;
-        stage_copy(rl * L,
-                   [&](int x) {
-                       const int64_t n = n0 + x;
-                       return p.period > 0 ? p.s[n % p.period] : (n < p.W ? p.s[n] : 0.0f);
-                   },
-                   [&](int x, float v) { ss[x] = v; });
+        stage_copy<NT>(rl * L,
+                       [&](int x) {
+                           const int64_t n = n0 + x;
+                           return p.period > 0 ? p.s[n % p.period] : (n < p.W ? p.s[n] : 0.0f);
+                       },
+                       [&](int x, float v) { ss[x] = v; });
         // kernel samples k'(c0 L - (L - 1) + x)
         const int64_t k0 = c0 * L - (L - 1);
-        stage_copy(tc * L + 2 * L - 1,
-                   [&](int x) {
-                       const int64_t n = k0 + x;
-                       return (n >= 0 && n < p.N) ? (p.reverse ? p.k[p.N - 1 - n] : p.k[n]) : 0.0f;
-                   },
-                   [&](int x, float v) { ks[x] = v; });
+        stage_copy<NT>(tc * L + 2 * L - 1,
+                       [&](int x) {
+                           const int64_t n = k0 + x;
+                           return (n >= 0 && n < p.N) ? (p.reverse ? p.k[p.N - 1 - n] : p.k[n]) : 0.0f;
+                       },
+                       [&](int x, float v) { ks[x] = v; });
         __syncthreads();
         // channels: X(l, i0 + ii) = sum_t s[(i0 + ii) L + t] C[t, l]
-        for (int x = tid; x < r * rl; x += kCT) {
+        for (int x = tid; x < r * rl; x += NT) {
             const int l = x / rl, ii = x - l * rl;
             float v = 0.0f;
             for (int t = 0; t < L; ++t) v = fmaf(ss[ii * L + t], p.C[t * L + l], v);
             xs[l * rlm + ii] = v;
         }
         // taps: H(q, l, c0 + cc) = sum_u D[l, u] k'((c0 + cc) L - q + u), zero past ntap
-        for (int x = tid; x < NPH * r * tc; x += kCT) {
+        for (int x = tid; x < NPH * r * tc; x += NT) {
             const int cc = x % tc, l = (x / tc) % r, q = x / (tc * r);
             float v = 0.0f;
             if (c0 + cc < p.ntap) {
@@ -281,11 +304,11 @@ __global__ __launch_bounds__(kCT) void corr_small_kernel(CorrSmallArgs p, int tc
         }
         __syncthreads();
         if (halo_on)
-            corr_tile<NPH, true>(xs, rlm, hs, tcmax, r, tc, w, lane, acc, halo);
+            corr_tile<NPH, OPT, NW, true>(xs, rlm, hs, tcmax, r, tc, w, lane, acc, halo);
         else
-            corr_tile<NPH, false>(xs, rlm, hs, tcmax, r, tc, w, lane, acc, halo);
+            corr_tile<NPH, OPT, NW, false>(xs, rlm, hs, tcmax, r, tc, w, lane, acc, halo);
     }
-    corr_finish<NPH>(lds, acc, halo, halo_on ? 1 : 0, a0, p.nrows, L, p.nout, p.y, nullptr);
+    corr_finish<NPH, OPT, NW>(lds, acc, halo, halo_on ? 1 : 0, a0, p.nrows, L, p.nout, p.y, nullptr);
 }
 
 // ---- block rate, longer blocks ----------------------------------------------
@@ -293,7 +316,7 @@ constexpr int kBlockRL = kTA + kBlockTC + 4;
 constexpr int block_lds_floats()
 {
     constexpr int stage = kBlockCH * kBlockRL + kBlockCH * kBlockTC;
-    return stage > finish_floats<1>() ? stage : finish_floats<1>();
+    return stage > finish_floats<1, kOPT, kNW>() ? stage : finish_floats<1, kOPT, kNW>();
 }
 
 // X(ch, i): SRC 0 = channel rows x[ch * xld + i] (valid i < xn);
@@ -415,12 +438,12 @@ __global__ __launch_bounds__(kCT) void corr_block_kernel(CorrBlockArgs p)
     for (int s = 0; s < nt; ++s) {
         const BlockTile t = tile(s);
         if (s + 1 < nt) block_tile_load<SRC>(p, a0, tile(s + 1), xv, hv);     // in flight during the contraction
-        corr_tile<1, false>(xs, kBlockRL, hs, kBlockTC, t.nch, t.tc, w, lane, acc, halo);
+        corr_tile<1, kOPT, kNW, false>(xs, kBlockRL, hs, kBlockTC, t.nch, t.tc, w, lane, acc, halo);
         __syncthreads();
         if (s + 1 < nt) block_tile_store<SRC>(tile(s + 1), xv, hv, xs, hs);
         __syncthreads();
     }
-    corr_finish<1>(lds, acc, halo, 2, a0, p.nd, p.L, p.nout, p.y, p.part + (int64_t)sp * p.nd);
+    corr_finish<1, kOPT, kNW>(lds, acc, halo, 2, a0, p.nd, p.L, p.nout, p.y, p.part + (int64_t)sp * p.nd);
 }
 
 // Sum of the channel-range partials (highest range first) for a tile of rows,
@@ -668,26 +691,38 @@ __global__ __launch_bounds__(kTapThreads) void kd_range_kernel(const float* __re
     }
 }
 
-template <int NPH>
-int launch_small_t(const CorrSmallArgs& a, hipStream_t s)
+template <int NPH, int OPT, int NW>
+int launch_small_cut(const CorrSmallArgs& a, hipStream_t s)
 {
     // the largest tap tile (a multiple of 32, at most the padded tap count)
     // whose staged tile fits the LDS budget
     const int nph = NPH;
+    constexpr int fin = finish_floats<NPH, OPT, NW>();
     const int64_t ntp32 = rup(rup(a.ntap, 8), 32);
-    const int budget = std::max(kSmallBudget, finish_floats<NPH>());
+    const int budget = std::max(kSmallBudget, fin);
     int tc = 32;
-    while (tc < 2048 && tc < ntp32 && small_stage_floats(a.L, a.r, nph, tc + 32) <= budget) tc += 32;
-    const size_t lds = 4 * (size_t)std::max(small_stage_floats(a.L, a.r, nph, tc), finish_floats<NPH>());
-    static size_t lds_allowed = 65536;    // per instantiation: raise the dynamic LDS limit when needed
-    if (lds > lds_allowed) {
-        if (hipFuncSetAttribute((const void*)corr_small_kernel<NPH>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return -1;
-        lds_allowed = lds;
-    }
-    hipLaunchKernelGGL(corr_small_kernel<NPH>, dim3((unsigned)cdiv(a.nrows, kTA)), dim3(kCT), lds, s, a, tc);
+    while (tc < 2048 && tc < ntp32 && small_stage_floats(64 * OPT, a.L, a.r, nph, tc + 32) <= budget) tc += 32;
+    const size_t lds = 4 * (size_t)std::max(small_stage_floats(64 * OPT, a.L, a.r, nph, tc), fin);
+    if (lds > 65536 && hipFuncSetAttribute((const void*)corr_small_kernel<NPH, OPT, NW>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return -1;
+    hipLaunchKernelGGL((corr_small_kernel<NPH, OPT, NW>), dim3((unsigned)cdiv(a.nrows, 64 * OPT)), dim3(64 * NW), lds,
+                       s, a, tc);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// Rows per workgroup: 512 on 4 waves from one workgroup a CU, else 128 rows on 8
+// waves while those fill most of the chip, else 64 rows on 16 (us for 512 / 128 / 64
+// rows: 8 blocks of 512 rows, N = 3582, L = r = 8: 272 / 80 / 57; 19, N = 600, L = 2, r = 1: 9.5 /
+// 5.6 / 5.7; 25, N = 1000, L = 8, r = 4, block rate: 19 / 8.5 / 7.6; 97, N = 1000, L = r = 2: 19.2 /
+// 12.3 / 27.8; 244, N = 3000, L = 8, r = 1: 34.5 / 34.4 / 73.8; 293, N = 600, L = 2, r = 1: 11.2 / 13.2 /
+// 42.4).
+template <int NPH>
+int launch_small_t(const CorrSmallArgs& a, hipStream_t s)
+{
+    if (cdiv(a.nrows, 512) >= 256) return launch_small_cut<NPH, 8, 4>(a, s);
+    if (cdiv(a.nrows, 128) >= 200) return launch_small_cut<NPH, 2, 8>(a, s);
+    return launch_small_cut<NPH, 1, 16>(a, s);
 }
 
 }  // namespace
