@@ -104,6 +104,8 @@ _SIGNATURES = {
 def lib():
     """The loaded library; raises if libprojgemm.so has not been built."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(_LIB_PATH):
@@ -135,8 +137,13 @@ def _prec(p) -> int:
 
 
 def _stream(stream=None) -> int:
+    """Handle of `stream`, by default the current device's current stream (read
+    without building a torch.cuda.Stream, which costs several microseconds: a
+    third of the submission of a small call)."""
     import torch
     if stream is None:
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
