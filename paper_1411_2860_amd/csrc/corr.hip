@@ -61,6 +61,9 @@ __device__ __forceinline__ void corr_taps(const float* __restrict__ xw, const fl
 #pragma unroll
         for (int i = 0; i < OPT; ++i) w[i] = xl[cb + i];
     }
+    // with one phase the copies that carry the window show (45.2 against 44.2 us)
+    constexpr int kUnroll = NPH == 1 ? 2 : 1;
+#pragma unroll kUnroll
     for (int c = cb; c < ce; c += 8) {
         if constexpr (OPT % 4 == 0) {
 #pragma unroll
