@@ -67,26 +67,10 @@ struct PackJob {
     // jj, t) at (jj * TCp + t) * RT + rr, filled by single-value direct loads
     // along the contiguous rows of the source.
     int tdma, RT;
+    int rw;             // FP8 tiles of one row per wave
     TIn* keep;          // plain copy of the projections (nullptr: none)
     int64_t keep_ld;
 };
-
-// ---- OCP FP8 E4M3 (1 sign, 4 exponent bits with bias 7, 3 mantissa bits,
-// largest finite 448, no infinities) with round-to-nearest-even; |v| <= 448.
-__device__ __forceinline__ unsigned fp8_e4m3_rne(float v)
-{
-    const unsigned sign = (__float_as_uint(v) >> 24) & 0x80u;
-    const float a = fabsf(v);
-    unsigned code;
-    if (a < 0.015625f) {                       // below 2^-6: subnormal steps of 2^-9
-        code = (unsigned)__float2uint_rn(a * 512.0f);   // 0 .. 8 (8 = smallest normal)
-    } else {
-        unsigned b = __float_as_uint(a);
-        b += 0x7FFFFu + ((b >> 20) & 1u);      // round the 23-bit mantissa to 3 bits
-        code = ((((b >> 23) & 0xFFu) - 120u) << 3) | ((b >> 20) & 7u);
-    }
-    return sign | code;
-}
 
 // ---- conversion of E accumulated values into one lane vector -------------
 
@@ -201,14 +185,23 @@ __device__ __forceinline__ float fp8_decode(unsigned c)
 // optionally the dequantised values.
 __device__ __forceinline__ void fp8_encode8(const float* v, float inv, float sc, unsigned& w0, unsigned& w1, float* deq)
 {
-    w0 = w1 = 0;
+    float x[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float x = fminf(fmaxf(v[e] * inv, -448.0f), 448.0f);
-        const unsigned c = fp8_e4m3_rne(x);
-        if (e < 4) w0 |= c << (8 * e);
-        else w1 |= c << (8 * (e - 4));
-        if (deq) deq[e] = fp8_decode(c) * sc;
+    for (int e = 0; e < 8; ++e) x[e] = fminf(fmaxf(v[e] * inv, -448.0f), 448.0f);
+    // OCP FP8 E4M3 (1 sign, 4 exponent bits with bias 7, 3 mantissa bits, largest
+    // finite 448, no infinities), round to nearest even; two values an
+    // instruction, into the low or the high half of the word
+    int c[2] = {0, 0};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        c[h] = __builtin_amdgcn_cvt_pk_fp8_f32(x[4 * h], x[4 * h + 1], c[h], false);
+        c[h] = __builtin_amdgcn_cvt_pk_fp8_f32(x[4 * h + 2], x[4 * h + 3], c[h], true);
+    }
+    w0 = (unsigned)c[0];
+    w1 = (unsigned)c[1];
+    if (deq) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) deq[e] = fp8_decode(((e < 4 ? w0 : w1) >> (8 * (e & 3))) & 0xFFu) * sc;
     }
 }
 
@@ -257,13 +250,151 @@ __device__ __forceinline__ void store_fp8_quarter(char* __restrict__ out, int64_
     }
 }
 
+// FP8 tile of 4 rows x 64 groups, rows contiguous along k: every wave
+// stages, contracts and stores one row by itself, without a barrier.  Lane =
+// group, PASS projections of the row in registers, each sum in ascending t.
+// Chunk t4 (4 indices) of group g lies at slot g TC/4 + (t4 ^ swizzle(g)), so
+// that the 16-byte reads of 16 neighbouring groups fall in distinct banks.
+// Bound: the source's bytes.  Tiles of 8 rows shared by four waves that each took
+// a quarter of the projections read every LDS value four times, in 64-byte runs
+// of the source between two barriers (9216 x 4096, L = 64, r = 8, 151 MB: 53.4 us);
+// a wave's own row needs neither, at 128-byte runs (42 us; with 64-byte runs
+// 43, whole groups of 256 bytes at half the wavefronts 47).
+// Taken for L > 8: a group of 4 or 8 indices leaves a wave's row too little to
+// have in flight (8192 x 4096, L = 4, r = 2: 84 us against 43 of the common
+// path; four rows a wave win that back but cost the longer groups their
+// wavefronts).
+__host__ __device__ constexpr bool fp8_row_waves(int L) { return L > 8; }
+// Floats of LDS per wave: the round, and afterwards the sums on their way to
+// the stores' lanes.
+__host__ __device__ constexpr int fp8_wave_floats(int TC, int PASS) { return 64 * (TC > PASS ? TC : PASS); }
+
+template <int PREC, int PASS>
+__device__ __forceinline__ void pack_tile_fp8(const PackJob<float>& J, int64_t tix)
+{
+    constexpr Layout ly = layout_of(PREC);
+    constexpr int KB = ly.KB, RB = ly.RB;
+    static_assert(KB == 64 && RB == 32, "lane = group");
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int L = J.L, r = J.r, TC = J.TC, ltc4 = J.ltc4, tcm = (1 << ltc4) - 1;
+    float* lds = reinterpret_cast<float*>(smem_raw) + wave * fp8_wave_floats(TC, PASS);
+    const int64_t rti = tix / J.ngt;
+    const int64_t j0 = (tix % J.ngt) * KB;
+    const int64_t p0 = rti * 4 + wave;
+    const int64_t rbi = p0 / RB;
+    const float* __restrict__ X = J.X;
+    using ConstF = const __attribute__((address_space(4))) float;
+    ConstF* coefc = (ConstF*)(J.coef);
+    const int sh = ltc4 < 4 ? 4 - ltc4 : 0;
+    auto swizzle = [&](int g) { return (g >> sh) & tcm; };
+    // this wave's LDS accesses before it done, later ones after it
+    auto fence = [&] {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+    };
+
+    auto stage = [&](int t0) {
+        const bool interior = p0 < J.P && (j0 + KB - 1) * L + t0 + TC <= J.K;
+        const float* __restrict__ base = X + p0 * J.ld + j0 * L + t0;
+        // source offset of slot `sl`
+        auto where = [&](int sl) -> int64_t {
+            const int gg = sl >> ltc4;
+            return (int64_t)gg * L + 4 * ((sl & tcm) ^ swizzle(gg));
+        };
+        fence();
+        if (J.dma4) {
+            const int n = 4 << ltc4;
+            for (int i = 0; i < n; ++i) {
+                const int64_t ko = where((i * 64 + lane) >> 2) + (lane & 3);
+                const float* src = base + ko;
+                if (!interior && (p0 >= J.P || j0 * L + t0 + ko >= J.K)) src = X;
+                lds_direct4(src, lds + i * 64);
+            }
+        } else {
+            const int n = 1 << ltc4;
+            for (int i = 0; i < n; ++i) {
+                const int64_t ko = where(i * 64 + lane);
+                const float* src = base + ko;
+                if (!interior && (p0 >= J.P || j0 * L + t0 + ko >= J.K)) src = X;
+                lds_direct16(src, lds + i * 256);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (!interior) {
+            // values outside the operand, read from X itself above, are zeros
+            const int n = 4 << ltc4;
+            for (int i = 0; i < n; ++i) {
+                const int64_t ko = where((i * 64 + lane) >> 2) + (lane & 3);
+                if (p0 >= J.P || j0 * L + t0 + ko >= J.K) lds[i * 64 + lane] = 0.0f;
+            }
+        }
+        fence();
+    };
+
+    const float* mine = lds + (lane << ltc4) * 4;
+    const int sw = swizzle(lane);
+    // of the stores: 8 groups of one of 8 projections a lane
+    const int g = lane & 7, lq = lane >> 3;
+    for (int lp = 0; lp < r; lp += PASS) {
+        float acc[PASS];
+#pragma unroll
+        for (int l = 0; l < PASS; ++l) acc[l] = 0.0f;
+        // coefficients through the constant address space (scalar loads of a whole
+        // row's PASS columns); the clamped columns of a last pass wider than the
+        // matrix belong to projections >= r, which are never stored
+        auto contract = [&](int t0, auto clamp) {
+#pragma unroll 2
+            for (int t4 = 0; t4 <= tcm; ++t4) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(mine + 4 * (t4 ^ sw));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    ConstF* cr = coefc + (int64_t)(t0 + 4 * t4 + i) * L + lp;
+#pragma unroll
+                    for (int l = 0; l < PASS; ++l) acc[l] += v[i] * cr[clamp ? min(l, L - 1 - lp) : l];
+                }
+            }
+        };
+        for (int t0 = 0; t0 < L; t0 += TC) {
+            stage(t0);
+            if (lp + PASS <= L) contract(t0, std::false_type{});
+            else contract(t0, std::true_type{});
+        }
+        fence();
+#pragma unroll
+        for (int l = 0; l < PASS; ++l) lds[l * 64 + lane] = acc[l];
+        fence();
+#pragma unroll
+        for (int i = 0; i < PASS; i += 8) {
+            const int ll = i + lq, l = lp + ll;
+            if (l >= r || ll >= PASS) continue;                    // the same for the 4 lanes of an MX block
+            const float* src = lds + ll * 64 + g * 8;
+            float v8[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v8[e] = src[e];
+            if (J.keep && p0 < J.P) {
+                float* dst = J.keep + p0 * J.keep_ld + (int64_t)l * J.Gp + j0 + g * 8;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) dst[e] = v8[e];
+            }
+            const int64_t tile = rbi * J.nkb + ((int64_t)l * J.Gp + j0) / KB;
+            store_fp8_quarter<PREC>(J.out, tile, (int)(p0 % RB), g, J.plane_stride, J.plane_bytes, v8);
+        }
+    }
+}
+
 // LAY: round layout in LDS -- 0 padded rows (register staging), 1 swizzled
 // (direct loads, rows contiguous along k), 2 transposed (direct loads from a
-// transposed source).
+// transposed source; for FP8, which has no such tile, the rows of pack_tile_fp8).
 template <typename TIn, int PREC, int RL, int NCH, int LAY>
 __device__ __forceinline__ void pack_tile(const PackJob<TIn>& J, int64_t tix)
 {
     constexpr Layout ly = layout_of(PREC);
+    if constexpr (LAY == 2 && ly.scales) {
+        pack_tile_fp8<PREC, 4 * NCH * RL>(J, tix);
+        return;
+    }
     constexpr int KB = ly.KB, RB = ly.RB;
     constexpr int Ec = Cmap<PREC>::Ec, NGc = Cmap<PREC>::NGc, TRc = Cmap<PREC>::TRc;
     using V4 = typename Vec4<TIn>::type;
@@ -805,6 +936,12 @@ PackJob<TIn> make_job(const PackArgs& a)
             tc *= 2;
         if (a.L % tc == 0 && tc > TC) TC = tc;
     }
+    if (std::is_same<TIn, float>::value && !a.trans && ly.scales && fp8_row_waves(a.L)) {
+        // longest runs of consecutive addresses that leave 20 waves a CU
+        int tc = 4;
+        while (tc * 2 <= a.L && a.L % (tc * 2) == 0 && tc * 2 <= 32) tc *= 2;
+        if (a.L % tc == 0) TC = tc;
+    }
     if (j.vec4 && TC % 4 != 0) j.vec4 = 0;
     j.TC = TC;
     j.TCp = (TC + 3) / 4 * 4;
@@ -819,6 +956,8 @@ PackJob<TIn> make_job(const PackArgs& a)
     j.swz = std::is_same<TIn, float>::value && !j.trans && TC % 4 == 0 && tc4 > 0 && (tc4 & (tc4 - 1)) == 0 &&
             (Cmap<PREC>::TRc * nc) % kPackThreads == 0 && Cmap<PREC>::TRc * nc <= 32 * kPackThreads;
     j.dma4 = j.swz && !j.vec4;
+    j.rw = ly.scales && j.swz && fp8_row_waves(a.L);
+    if (j.rw) j.nrt = g.nrb * (ly.RB / 4);
     j.lnc = j.ltc4 = j.sm = 0;
     if (j.swz) {
         while ((1 << j.lnc) < nc) ++j.lnc;
@@ -837,12 +976,13 @@ PackJob<TIn> make_job(const PackArgs& a)
 
 // Round layout of a job (the LAY of pack_tile) and its LDS elements.
 template <typename TIn>
-int job_layout(const PackJob<TIn>& j) { return j.swz ? 1 : (j.tdma ? 2 : 0); }
+int job_layout(const PackJob<TIn>& j) { return j.rw ? 2 : (j.swz ? 1 : (j.tdma ? 2 : 0)); }
 
 template <typename TIn, int PREC>
 size_t round_lds_elems(const PackJob<TIn>& j, int lay)
 {
     if (lay == 1) return (size_t)Cmap<PREC>::TRc * ((size_t)4 << j.lnc);
+    if (j.rw) return 4 * ((size_t)4 << j.lnc);
     if (lay == 2) return (size_t)layout_of(PREC).KB * j.TCp * j.RT;
     return (size_t)Cmap<PREC>::TRc * j.RS;
 }
@@ -888,6 +1028,8 @@ int launch_t(const PackArgs* a, int n, hipStream_t s)
     size_t lds = std::max(round_lds_elems<TIn, PREC>(ja, lay), round_lds_elems<TIn, PREC>(jb, lay)) * sizeof(TIn);
     if constexpr (pack_mfma<TIn, PREC, RL, NCH>())
         lds = std::max(lds, (size_t)16 * pack_mfma_ds<PREC>() * sizeof(float));
+    if constexpr (layout_of(PREC).scales)
+        if (lay == 2) lds = std::max(lds, (size_t)4 * fp8_wave_floats(0, 4 * NCH * RL) * sizeof(float));
     if (na + nb > 0x7fffffff) return -2;
     return launch_lay<TIn, PREC, RL, NCH, false>(lay, dim3((unsigned)(na + nb)), lds, s, ja, jb, na);
 }
@@ -1319,6 +1461,8 @@ int launch_grouped_t(const PackArgs* a, int n, void* table, hipStream_t s)
         size_t lds = lds_e[o] * sizeof(TIn);
         if constexpr (pack_mfma<TIn, PREC, RL, NCH>())
             lds = std::max(lds, (size_t)16 * pack_mfma_ds<PREC>() * sizeof(float));
+        if constexpr (layout_of(PREC).scales)
+            if (order[o] == 2) lds = std::max(lds, (size_t)4 * fp8_wave_floats(0, 4 * NCH * RL) * sizeof(float));
         const int e = launch_lay<TIn, PREC, RL, NCH, true>(order[o], dim3((unsigned)grid), lds, s,
                                                            (const PackJob<TIn>*)t + start[o], (const int64_t*)pre,
                                                            start[o + 1] - start[o]);
