@@ -63,8 +63,12 @@ typedef enum {
  * (FP64 for PJ_F64) and rounded to the mode's operand format.
  *   PJ_F32  : FP32 operands and accumulation; larger outputs contract on the
  *             BF16 matrix cores with every operand as the exact sum of three
- *             BF16 values (six exact products; tiles holding values such a sum
- *             cannot carry use the FP32 instructions);
+ *             BF16 values.  Six of the nine exact products are formed; the three
+ *             left out are below 2^-24 of the product together.  The error
+ *             against FP64 is no larger than the FP32 instructions' (0.3 to 0.9
+ *             of it), except where a row holds a single value that is not zero:
+ *             one unit in the last place instead of half.  Tiles holding
+ *             values such a sum cannot carry use the FP32 instructions;
  *   PJ_BF16 / PJ_F16   : one rounded operand, FP32 accumulation;
  *   PJ_BF16X3 / PJ_F16X3: x = hi + lo split, R = hi*hi + hi*lo + lo*hi,
  *                         FP32 accumulation (about FP32-level error);

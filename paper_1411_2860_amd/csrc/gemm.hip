@@ -762,16 +762,25 @@ __device__ __forceinline__ void gemm_tile_dma_ra(
 
 // FP32 on the BF16 matrix cores.  An FP32 value is the exact sum of three
 // BF16 values h + m + l (8 significant bits each, round to nearest), and
-// a b = h h' + (h m' + m h') + (m m' + h l' + l h') up to terms below 2^-26
-// |a b|: six BF16 products, every one exact, accumulated in FP32.  The BF16
-// instructions do 16 times the work of the FP32 ones per cycle, so six of them
-// still run 2.7 times as fast, with fewer roundings of the accumulator (one per
-// instruction of 16 indices instead of one per index).  Error against FP64
-// measured at 0.4 .. 0.9 of the FP32 instructions' (image, normal, positive and
-// log-normal operands, 1 to 64 of 64 projections).  Bound by the BF16 matrix
-// pipe, which sustains about 1.3 PFLOP/s here: 1024 x 8192 outputs, contraction
-// 4096: 341 us = 1.21 PFLOP/s of BF16 products (482 us on the FP32
-// instructions), contraction 1024: 92.6 us (127 us).
+// a b = h h' + (h m' + m h') + (m m' + h l' + l h') up to m l' + l m' + l l',
+// below 2^-25 |a b|: six BF16 products, every one exact.  The BF16 instructions do
+// 16 times the work of the FP32 ones per cycle, so six of them still run 2.7 times
+// as fast.
+//
+// Rounding.  The matrix cores round an accumulator with every instruction, more
+// coarsely than the FP32 ones round theirs with every index, so h h' and the five
+// smaller products have accumulators of their own, added up once at the end: the
+// large sum is then rounded once per instruction of 16 indices.  With one
+// accumulator for all six the error exceeded the FP32 instructions' wherever an
+// instruction adds few terms (rows with one value in ten not zero, 512 indices:
+// 0.84 against 0.47; 2 groups, 64 projections, positive values: 3.2 against 2.8; all
+// in rms units of 2^-24 of the sum of magnitudes).  With two: 0.19 and 1.2; normal
+// values, 2 / 64 / 2048 terms: 0.37 / 0.16 / 0.16 (FP32 instructions 0.44 / 0.47 / 0.47);
+// log-normal 0.45 / 0.68 / 1.6 (0.48 / 1.4 / 4.4).  A row with a single value that is
+// not zero keeps the three missing products' share: rms 0.436 against 0.425, at most 1.7
+// against 1.0.  Contractions of kSplitMinKb k-blocks, where one or two terms
+// may be all there is, stay on the FP32 instructions; they are bound by the
+// output anyway.
 //
 // The packed operands stay FP32.  Per stage of KS x 16 indices each wave loads
 // its share of the workgroup's tiles into registers two stages ahead (two FP32
@@ -784,7 +793,9 @@ __device__ __forceinline__ void gemm_tile_dma_ra(
 // round to a BF16 infinity leave a NaN in the products they reach; values below
 // 2^-102 (whose l would fall off the BF16 range) are noted while splitting.  A
 // workgroup that sees either in the rows and columns it stores computes its
-// tile again with the FP32 instructions.
+// tile again with the FP32 instructions (so the last bits of a row can depend on
+// the rows that share its tile).
+constexpr int kSplitMinKb = 2;
 constexpr unsigned kSplitTiny = (127u - 102u) << 24;      // 2^-102, shifted left by the sign bit
 
 __device__ __forceinline__ void split3(const f32x4& u, const f32x4& v, bf16x8 (&o)[3], unsigned& least)
@@ -822,6 +833,11 @@ __device__ __forceinline__ void gemm_tile_split(
     constexpr int PER_W = NT * KS / NW;            // 16-index fragments split per wave and stage
     constexpr int STAGE = NT * KS * 3 * 64;        // 16-byte chunks of a stage
     static_assert(NT * KS % NW == 0, "every wave splits the same number of fragments");
+    if (nkb <= kSplitMinKb) {
+        gemm_tile<P_F32, WM, WN, WAVES_M, WAVES_N>(X, x_nrb, x_nkb, 0, 0, Y, y_nrb, y_nkb, 0, 0, nkb, kb_lo, P, Q, R,
+                                                   ldr, beta, tm, tn);
+        return;
+    }
     extern __shared__ __align__(16) unsigned char smem_raw[];
     bf16x8* lds = reinterpret_cast<bf16x8*>(smem_raw);
     const int lane = threadIdx.x & 63;
@@ -876,13 +892,13 @@ __device__ __forceinline__ void gemm_tile_split(
             for (int pl = 0; pl < 3; ++pl) lds[buf * STAGE + (u * 3 + pl) * 64 + lane] = o[pl];
         }
     };
-    f32x16 acc[WM][WN];
+    f32x16 acc[WM][WN], low[WM][WN];               // sums of h h' and of the five smaller products
 #pragma unroll
     for (int a = 0; a < WM; ++a)
 #pragma unroll
         for (int b = 0; b < WN; ++b)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc[a][b][j] = 0.0f;
+            for (int j = 0; j < 16; ++j) acc[a][b][j] = low[a][b][j] = 0.0f;
     auto contract = [&](int buf) {
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
@@ -902,9 +918,10 @@ __device__ __forceinline__ void gemm_tile_split(
 #pragma unroll
                 for (int a = 0; a < WM; ++a)
 #pragma unroll
-                    for (int b = 0; b < WN; ++b)
-                        acc[a][b] =
-                            __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a][pa[q]], fb[b][pb[q]], acc[a][b], 0, 0, 0);
+                    for (int b = 0; b < WN; ++b) {
+                        f32x16& sum = q < 5 ? low[a][b] : acc[a][b];
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a][pa[q]], fb[b][pb[q]], sum, 0, 0, 0);
+                    }
         }
     };
     Raw r0, r1;
@@ -940,6 +957,7 @@ __device__ __forceinline__ void gemm_tile_split(
             for (int j = 0; j < 16; ++j) {
                 int row, col;
                 acc_pos<32>(j, lane, row, col);
+                acc[a][b][j] += low[a][b][j];
                 if ((rb0 + a) * 32 + row < P && (cb0 + b) * 32 + col < Q) z = fmaf(acc[a][b][j], 0.0f, z);
             }
     bool bad = z != z;
@@ -1297,8 +1315,8 @@ int launch_gemm_t(const GemmArgs& a, hipStream_t s)
 // blocks per wave along M, along N; waves along M, along N; minimum resident
 // workgroups per CU).  The workgroup tile is RB*WM*WAVES_M x RB*WN*WAVES_N.
 // FP8 runs the LDS kinds as direct.  FP32 runs the two kind 4 tiles (16 and 17) as
-// kind 6, three-way split operands on the BF16 instructions: the same tiles at
-// 0.7 of the time (1024 x 8192, 128 k-blocks: 92.6 against 127 us).
+// kind 6, three-way split operands on the BF16 instructions, in the same tiles
+// (17 on eight waves of 32 x 64 outputs): 0.7 of the time.
 constexpr bool split_config(int prec, int cfg) { return prec == P_F32 && (cfg == 16 || cfg == 17); }
 #define PJ_GEMM_CONFIGS(X)   \
     X(0, 0, 2, 2, 2, 2, 2)   \
@@ -1360,7 +1378,7 @@ int launch_grouped_cfg(const GroupedProblem* probs, const GroupedItem* items, in
     case i: \
         if constexpr (!split_config(PREC, i)) \
             return launch_grouped_t<k_, PREC, a_, b_, c_, d_, o_>(probs, items, nitems, nbig, cus, s); \
-        else if constexpr (i == 17) return launch_grouped_t<6, PREC, 1, 2, 4, 2, 1>(probs, items, nitems, nbig, cus, s); \
+        else if constexpr (i == 17) return launch_grouped_t<6, PREC, 1, 2, 4, 2, 4>(probs, items, nitems, nbig, cus, s); \
         else return launch_grouped_t<6, PREC, a_, b_, c_, d_, o_>(probs, items, nitems, nbig, cus, s);
         PJ_GEMM_CONFIGS(PJ_CFG_CASE)
 #undef PJ_CFG_CASE
@@ -1375,7 +1393,7 @@ int launch_cfg(const GemmArgs& a, int cfg, hipStream_t s)
 #define PJ_CFG_CASE(i, k_, a_, b_, c_, d_, o_) \
     case i: \
         if constexpr (!split_config(PREC, i)) return launch_gemm_t<k_, PREC, a_, b_, c_, d_, o_>(a, s); \
-        else if constexpr (i == 17) return launch_gemm_t<6, PREC, 1, 2, 4, 2, 1>(a, s); \
+        else if constexpr (i == 17) return launch_gemm_t<6, PREC, 1, 2, 4, 2, 4>(a, s); \
         else return launch_gemm_t<6, PREC, a_, b_, c_, d_, o_>(a, s);
         PJ_GEMM_CONFIGS(PJ_CFG_CASE)
 #undef PJ_CFG_CASE
@@ -1427,17 +1445,13 @@ int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb)
     // small problems: smaller tiles so that the grid still covers the chip
     const int64_t tiles128 = cdiv(P, 128) * cdiv(Q, 128);
     if (prec == P_F32) {
-        // The split 128 x 128 tile (one workgroup a CU holds its rate) from
-        // more tiles than half the CUs: 1003 x 3001, 102 k-blocks (192 tiles) 51.5 ->
-        // 38.7 us, 2048 x 2048, 128 k-blocks (256 tiles) 80 -> 53 us; at 128 tiles and
-        // below the 64 x 64 tile has more CUs at work (4096 x 512, 512 k-blocks: 150
-        // against 156 us; 512 x 2048, 128 k-blocks: 23.9 against 42.8 us).  256 x 128 where
-        // those tiles cover the chip and a contraction of 64 k-blocks pays for
-        // its longer first stage (1024 x 8192: 16 k-blocks 21.1 against 20.0 us, 32: 30.0
-        // and 30.0, 64: 51.9 and 52.8, 128: 92.6 and 97.6, 512: 341 and 366; the FP32
-        // instructions need 25.6, 41, 75, 127 and 482 us).
-        if (tiles128 <= 128) return 5;
-        return cdiv(P, 256) * cdiv(Q, 128) >= 256 && nkb >= 64 ? 16 : 17;
+        // The split 128 x 128 tile (two workgroups a CU) from more tiles than half
+        // the CUs: 1003 x 3001, 102 k-blocks (192 tiles) 50.3 -> 39.6 us, 2048 x 2048, 128
+        // k-blocks (256 tiles) 79 -> 56 us, 1024 x 8192, 128 and 512 k-blocks 144 -> 97 and
+        // 538 -> 356 us; at 128 tiles and below the 64 x 64 tile has more CUs at work (4096 x
+        // 512, 512 k-blocks: 150 against 156 us; 512 x 2048, 128 k-blocks: 23.9 against 42.8 us).
+        // 256 x 128 tiles hold one workgroup a CU: 105 and 382 us for the two long ones.
+        return tiles128 <= 128 ? 5 : 17;
     }
     if (tiles128 < 256) return 5;
     // (measured on the recognition and backward shapes, one timing per config)
@@ -1462,14 +1476,15 @@ int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb)
 // call: BF16x3 1042 -> 843 us and BF16 765 -> 648 us against the direct
 // 128 x 128 tile of before; 128 x 128 rings 855 and 670; r = 16 BF16x3
 // contraction 3.54 -> 1.66 ms; up to sides of 512 the choice does not matter,
-// up to 2048 it is 251 -> 230 us).  FP32: the split tile of 256 x 128
-// (r = 1 / 4 / 16: 629 / 1200 / 3800 us, 128 x 128: 672 / 1350 / 4210, the rings on
-// the FP32 instructions 697 / 1540 / 4930, the direct tile of before 1785 us at
-// r = 4).  FP64 and FP8 have no ring: direct 128 x 128 blocks.
+// up to 2048 it is 251 -> 230 us).  FP32: the split tile of 128 x 128 (same
+// problems, r = 1 / 4 / 16: 621 / 1333 / 4166 us; 256 x 128: 766 / 1463 / 4261; the direct tile
+// on the FP32 instructions 787 / 1923 / 6102).  FP64 and FP8 have no ring: direct
+// 128 x 128 blocks.
 int gemm_grouped_default_config(int prec)
 {
     switch (prec) {
-    case P_F32: case P_BF16: case P_BF16X3: case P_F16: case P_F16X3: return 16;
+    case P_F32: return 17;
+    case P_BF16: case P_BF16X3: case P_F16: case P_F16X3: return 16;
     default: return 0;
     }
 }
@@ -1504,7 +1519,7 @@ void gemm_parts_plan(int prec, int64_t P, int64_t Q, int64_t nkb, int* cfg, int*
     if (tiles > 128) return;
     const int64_t n = std::min<int64_t>(std::min<int64_t>(256 / tiles, nkb / (prec == P_F32 ? 64 : 32)), 8);
     if (n < 2 || tiles * n < 128) return;
-    *cfg = 16;
+    *cfg = prec == P_F32 ? 17 : 16;
     *nparts = (int)n;
 }
 
