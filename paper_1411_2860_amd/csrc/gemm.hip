@@ -791,12 +791,16 @@ __device__ __forceinline__ void gemm_tile_dma_ra(
 //
 // Values the split cannot carry go another way: infinities, NaN and values that
 // round to a BF16 infinity leave a NaN in the products they reach; values below
-// 2^-102 (whose l would fall off the BF16 range) are noted while splitting.  A
-// workgroup that sees either in the rows and columns it stores computes its
-// tile again with the FP32 instructions (so the last bits of a row can depend on
-// the rows that share its tile).
+// 2^-110, whose last bit 2^-133 a subnormal BF16 value just holds, are noted while
+// splitting.  A workgroup that sees either in the rows and columns it stores
+// computes its tile with the FP32 instructions in the interleaved copy ring (so
+// the last bits of a row can depend on the rows that share its tile).  Small
+// values are looked for after 2, 8, 32 ... stages, the rest at the end.  1024 x 8192,
+// 128 k-blocks: 97 us without such a value, 134 us with one below 2^-110 in every
+// tile (140 us on the FP32 instructions alone; 237 us in the direct body after the
+// whole split), about 220 us with a NaN or an infinity in every tile.
 constexpr int kSplitMinKb = 2;
-constexpr unsigned kSplitTiny = (127u - 102u) << 24;      // 2^-102, shifted left by the sign bit
+constexpr unsigned kSplitTiny = (127u - 110u) << 24;      // 2^-110, shifted left by the sign bit
 
 __device__ __forceinline__ void split3(const f32x4& u, const f32x4& v, bf16x8 (&o)[3], unsigned& least)
 {
@@ -821,6 +825,20 @@ constexpr int gemm_split_ks()
     return nt >= 12 || nt <= 4 || nt % (WAVES_M * WAVES_N) != 0 ? 2 : 1;
 }
 
+// The FP32 body of the tiles the split leaves: the interleaved copy ring.  The
+// workgroup's LDS is free again when it returns.
+template <int WM, int WN, int WAVES_M, int WAVES_N>
+__device__ __forceinline__ void gemm_tile_unsplit(
+    const char* __restrict__ X, int64_t x_nrb, int64_t x_nkb, const char* __restrict__ Y, int64_t y_nrb,
+    int64_t y_nkb, int64_t nkb, int64_t kb_lo, int64_t P, int64_t Q, float* __restrict__ R, int64_t ldr, float beta,
+    int64_t tm, int64_t tn)
+{
+    constexpr int KS = gemm_split_ks<WM, WN, WAVES_M, WAVES_N>();
+    gemm_tile_dma_ra<P_F32, WM, WN, WAVES_M, WAVES_N, 4, KS, true>(X, x_nrb, x_nkb, 0, Y, y_nrb, y_nkb, 0, nkb, kb_lo,
+                                                                   P, Q, R, ldr, beta, tm, tn);
+    __syncthreads();         // no copy of another wave is still on its way into the LDS
+}
+
 template <int WM, int WN, int WAVES_M, int WAVES_N>
 __device__ __forceinline__ void gemm_tile_split(
     const char* __restrict__ X, int64_t x_nrb, int64_t x_nkb, const char* __restrict__ Y, int64_t y_nrb,
@@ -833,11 +851,6 @@ __device__ __forceinline__ void gemm_tile_split(
     constexpr int PER_W = NT * KS / NW;            // 16-index fragments split per wave and stage
     constexpr int STAGE = NT * KS * 3 * 64;        // 16-byte chunks of a stage
     static_assert(NT * KS % NW == 0, "every wave splits the same number of fragments");
-    if (nkb <= kSplitMinKb) {
-        gemm_tile<P_F32, WM, WN, WAVES_M, WAVES_N>(X, x_nrb, x_nkb, 0, 0, Y, y_nrb, y_nkb, 0, 0, nkb, kb_lo, P, Q, R,
-                                                   ldr, beta, tm, tn);
-        return;
-    }
     extern __shared__ __align__(16) unsigned char smem_raw[];
     bf16x8* lds = reinterpret_cast<bf16x8*>(smem_raw);
     const int lane = threadIdx.x & 63;
@@ -925,10 +938,13 @@ __device__ __forceinline__ void gemm_tile_split(
         }
     };
     Raw r0, r1;
-    gload(0, r0);
-    gload(1, r1);
-    park(0, 0, r0);
-    __syncthreads();
+    bool again = nkb <= kSplitMinKb;               // the tile is for the FP32 instructions
+    if (!again) {
+        gload(0, r0);
+        gload(1, r1);
+        park(0, 0, r0);
+        __syncthreads();
+    }
     // stage st in buffer st & 1; stage st + 1 is in registers, st + 2 on its way
     auto step = [&](int st, int buf, Raw& next, Raw& far) {
         gload(st + 2, far);
@@ -937,43 +953,58 @@ __device__ __forceinline__ void gemm_tile_split(
         park(st + 1, buf ^ 1, next);
         __syncthreads();
     };
-    int st = 0;
-    for (; st + 1 < nst; st += 2) {
+    // Whether any wave of the workgroup has seen something.  The flags lie behind
+    // the stages; the last check has flags of its own, since no barrier may
+    // stand between it and the check before (those are stages apart).
+    int* flags = reinterpret_cast<int*>(lds + 2 * STAGE);
+    auto any_wave = [&](bool mine, int* flag) {
+        const bool w = __builtin_amdgcn_ballot_w64(mine) != 0;
+        if (lane == 0) flag[wave] = w;
+        __syncthreads();
+        int any = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) any |= flag[i];
+        return __builtin_amdgcn_readfirstlane(any) != 0;
+    };
+    auto tiny = [&] {
+        bool t = false;
+#pragma unroll
+        for (int i = 0; i < PER_W; ++i) t |= live[i] && least[i] < kSplitTiny - 1u;
+        return t;
+    };
+    int st = 0, check = 2;
+    for (; st + 1 < nst && !again; st += 2) {
         step(st, 0, r1, r0);
         step(st + 1, 1, r0, r1);
+        if (st + 2 == check) {                      // 2, 8, 32, ...: no long contraction in vain
+            again = any_wave(tiny(), flags);
+            check *= 4;
+        }
     }
-    if (st < nst) {
-        contract(0);
-        __syncthreads();
-    }
-    // does the tile hold a value the split could not carry?
     const int64_t rb0 = rbB + wm * WM, cb0 = cbB + wn * WN;
-    float z = 0.0f;
+    if (!again) {
+        if (st < nst) {
+            contract(0);
+            __syncthreads();
+        }
+        // does the tile hold a value the split could not carry?
+        float z = 0.0f;
 #pragma unroll
-    for (int a = 0; a < WM; ++a)
+        for (int a = 0; a < WM; ++a)
 #pragma unroll
-        for (int b = 0; b < WN; ++b)
+            for (int b = 0; b < WN; ++b)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                int row, col;
-                acc_pos<32>(j, lane, row, col);
-                acc[a][b][j] += low[a][b][j];
-                if ((rb0 + a) * 32 + row < P && (cb0 + b) * 32 + col < Q) z = fmaf(acc[a][b][j], 0.0f, z);
-            }
-    bool bad = z != z;
-#pragma unroll
-    for (int i = 0; i < PER_W; ++i) bad |= live[i] && least[i] < kSplitTiny - 1u;
-    int* flag = reinterpret_cast<int*>(smem_raw);
-    const bool wbad = __builtin_amdgcn_ballot_w64(bad) != 0;
-    if (lane == 0) flag[wave] = wbad;
-    __syncthreads();
-    int any = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) any |= flag[w];
-    __syncthreads();                               // the flags are read before a next item's first stage
-    if (__builtin_amdgcn_readfirstlane(any))
-        gemm_tile<P_F32, WM, WN, WAVES_M, WAVES_N>(X, x_nrb, x_nkb, 0, 0, Y, y_nrb, y_nkb, 0, 0, nkb, kb_lo, P, Q, R,
-                                                   ldr, beta, tm, tn);
+                for (int j = 0; j < 16; ++j) {
+                    int row, col;
+                    acc_pos<32>(j, lane, row, col);
+                    acc[a][b][j] += low[a][b][j];
+                    if ((rb0 + a) * 32 + row < P && (cb0 + b) * 32 + col < Q) z = fmaf(acc[a][b][j], 0.0f, z);
+                }
+        again = any_wave(z != z || tiny(), flags + NW);
+    }
+    if (again)
+        gemm_tile_unsplit<WM, WN, WAVES_M, WAVES_N>(X, x_nrb, x_nkb, Y, y_nrb, y_nkb, nkb, kb_lo, P, Q, R, ldr, beta, tm,
+                                                    tn);
     else
         store_tile<P_F32, WM, WN>(acc, lane, rb0, cb0, P, Q, R, ldr, beta);
 }
@@ -1018,7 +1049,8 @@ template <int KIND, int PREC, int WM, int WN, int WAVES_M, int WAVES_N>
 constexpr size_t gemm_lds_bytes()
 {
     if constexpr (KIND == 6 && PREC == P_F32)
-        return 2ull * gemm_split_ks<WM, WN, WAVES_M, WAVES_N>() * (WM * WAVES_M + WN * WAVES_N) * 3 * 1024;
+        return 2ull * gemm_split_ks<WM, WN, WAVES_M, WAVES_N>() * (WM * WAVES_M + WN * WAVES_N) * 3 * 1024 +
+               8ull * WAVES_M * WAVES_N;                       // and two flags a wave
     else if constexpr (KIND >= 3 && KIND <= 5 && sizeof(typename MT<PREC>::frag) == 16)
         return 4ull * gemm_lds_ks<PREC, WM, WN, WAVES_M, WAVES_N>() * (WM * WAVES_M + WN * WAVES_N) *
                MT<PREC>::PLANES * 1024;
