@@ -1477,13 +1477,24 @@ int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb)
     // small problems: smaller tiles so that the grid still covers the chip
     const int64_t tiles128 = cdiv(P, 128) * cdiv(Q, 128);
     if (prec == P_F32) {
-        // The split 128 x 128 tile (two workgroups a CU) from more tiles than half
-        // the CUs: 1003 x 3001, 102 k-blocks (192 tiles) 50.3 -> 39.6 us, 2048 x 2048, 128
-        // k-blocks (256 tiles) 79 -> 56 us, 1024 x 8192, 128 and 512 k-blocks 144 -> 97 and
-        // 538 -> 356 us; at 128 tiles and below the 64 x 64 tile has more CUs at work (4096 x
-        // 512, 512 k-blocks: 150 against 156 us; 512 x 2048, 128 k-blocks: 23.9 against 42.8 us).
-        // 256 x 128 tiles hold one workgroup a CU: 105 and 382 us for the two long ones.
-        return tiles128 <= 128 ? 5 : 17;
+        // The split 128 x 128 tile (17; two workgroups a CU) against the 64 x 64 one (5).
+        // Up to half a CU's worth of them, 5 has more CUs at work (4096 x 512, 512
+        // k-blocks: 150 against 156 us; 512 x 2048, 128 k-blocks: 23.9 against 42.8 us).  Where
+        // an edge leaves a quarter or more of the large tiles' area empty, 5 does
+        // less work: 64 x 20000, 8 and 96 k-blocks 5.9 and 29 against 8.5 and 37 us; 129 x
+        // 17000, 2 and 32 k-blocks 6.2 and 23 against 8.6 and 26 us.
+        const int64_t tiles64 = cdiv(P, 64) * cdiv(Q, 64);
+        if (tiles128 <= 128 || tiles64 <= 3 * tiles128) return 5;
+        // Otherwise 17 from the contraction that pays for its longer first stage:
+        // up to one tile a CU by the work of 5 (1500 x 1500, 8 / 16 / 32 / 96 k-blocks: 8.4 /
+        // 12.0 / 19.4 / 47 against 9.1 / 12.0 / 17.3 / 37 us; 1920 x 1920, 4 / 8: 8.1 / 10.5
+        // against 8.4 / 9.9 us), while some CUs hold two tiles and some one from 12
+        // k-blocks (2000 x 2100, 4 / 8 / 16 / 32: 9.3 / 12.3 / 18.2 / 29 against 11.4 / 13.4 / 18.0 /
+        // 27 us), above from 2 (1024 x 8192, 1 / 2 / 128 / 512: 9.7 / 11.5 / 155 / 600 against 10.0 /
+        // 11.0 / 97 / 356 us).  256 x 128 tiles (16) hold one workgroup a CU: 105 and 382 us
+        // for the last two.
+        if (tiles128 <= 256) return tiles64 * nkb >= 7000 ? 17 : 5;
+        return nkb >= (tiles128 < 512 ? 12 : 2) ? 17 : 5;
     }
     if (tiles128 < 256) return 5;
     // (measured on the recognition and backward shapes, one timing per config)

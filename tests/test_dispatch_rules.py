@@ -1,0 +1,38 @@
+"""Rules that choose a kernel by size, called in the library without a GPU
+(their C++ names): each figure beside a rule is a choice it has to make."""
+import ctypes
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def rule():
+    from paper_1411_2860_amd import projgemm as pg
+    L = pg.lib()
+
+    def get(name, res, *args):
+        f = getattr(L, name)
+        f.restype, f.argtypes = res, list(args)
+        return f
+    return get
+
+
+F64, F32, BF16 = 0, 1, 2
+SPLIT128, FP32_64 = 17, 5
+
+
+@pytest.mark.parametrize("P,Q,nkb,cfg", [
+    # an edge leaves a quarter or more of the 128 x 128 tiles' area empty
+    (1, 20000, 32, FP32_64), (64, 20000, 8, FP32_64), (64, 20000, 96, FP32_64), (20000, 64, 96, FP32_64),
+    (129, 8400, 96, FP32_64), (129, 17000, 2, FP32_64), (192, 17000, 32, FP32_64), (32, 70000, 32, FP32_64),
+    # short contractions
+    (1500, 1500, 1, FP32_64), (1500, 1500, 8, FP32_64), (1024, 2176, 4, FP32_64), (2000, 2100, 4, FP32_64),
+    (4096, 4096, 1, FP32_64),
+    # full tiles, long contractions
+    (96, 17000, 32, SPLIT128), (1500, 1500, 32, SPLIT128), (1920, 1920, 8, SPLIT128), (2000, 2100, 32, SPLIT128),
+    (193, 17000, 32, SPLIT128), (1024, 8192, 2, SPLIT128), (1024, 8192, 128, SPLIT128), (1003, 3001, 102, SPLIT128),
+    # too few tiles
+    (512, 2048, 128, FP32_64), (4096, 512, 512, FP32_64)])
+def test_fp32_tile(rule, P, Q, nkb, cfg):
+    f = rule("_ZN2pj19gemm_default_configEilll", ctypes.c_int, ctypes.c_int, *[ctypes.c_long] * 3)
+    assert f(F32, P, Q, nkb) == cfg
