@@ -89,6 +89,7 @@ struct CorrSmallArgs {
 };
 int launch_corr_small(const CorrSmallArgs& a, hipStream_t s);
 int corr_small_max_L();
+int corr_small_rows(int64_t nrows, int L, int r, int block);      // rows per workgroup
 int corr_rows_per_tile();
 
 // Block rate, longer blocks: yd[a] = sum_ch sum_c X(ch, a + c) H(ch, c),

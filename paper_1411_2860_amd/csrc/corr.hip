@@ -714,21 +714,38 @@ int launch_small_cut(const CorrSmallArgs& a, hipStream_t s)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Rows per workgroup: 512 on 4 waves from one workgroup a CU, else 128 rows on 8
-// waves while those fill most of the chip, else 64 rows on 16 (us for 512 / 128 / 64
-// rows: 8 blocks of 512 rows, N = 3582, L = r = 8: 272 / 80 / 57; 19, N = 600, L = 2, r = 1: 9.5 /
-// 5.6 / 5.7; 25, N = 1000, L = 8, r = 4, block rate: 19 / 8.5 / 7.6; 97, N = 1000, L = r = 2: 19.2 /
-// 12.3 / 27.8; 244, N = 3000, L = 8, r = 1: 34.5 / 34.4 / 73.8; 293, N = 600, L = 2, r = 1: 11.2 / 13.2 /
-// 42.4).
 template <int NPH>
 int launch_small_t(const CorrSmallArgs& a, hipStream_t s)
 {
-    if (cdiv(a.nrows, 512) >= 256) return launch_small_cut<NPH, 8, 4>(a, s);
-    if (cdiv(a.nrows, 128) >= 200) return launch_small_cut<NPH, 2, 8>(a, s);
-    return launch_small_cut<NPH, 1, 16>(a, s);
+    switch (corr_small_rows(a.nrows, a.L, a.r, a.block)) {
+    case 512: return launch_small_cut<NPH, 8, 4>(a, s);
+    case 128: return launch_small_cut<NPH, 2, 8>(a, s);
+    default:  return launch_small_cut<NPH, 1, 16>(a, s);
+    }
 }
 
 }  // namespace
+
+// Rows per workgroup: 64 on 16 waves while one workgroup a CU holds them all, 128 on 8
+// waves while two a CU do, else 512 on 4.  A cut is good for whole rounds of
+// workgroups only: 64 rows cost twice as much from 257 workgroups on, 128 rows a
+// round more at each multiple of 256.  us for 512 / 128 / 64 rows, in blocks of 512
+// rows: L = r = 1, N = 300, full rate, 4 blocks 6.4 / 4.9 / 4.9, 32: 6.4 / 4.8 / 5.2, 33: 6.4 /
+// 4.9 / 8.7, 128: 6.4 / 6.4 / 16.5, 140: 6.5 / 7.5 / 20; L = 8, r = 4, N = 1000, 32 blocks: 42 /
+// 16 / 12.9, 48: 42 / 16.4 / 23.9, 128: 42.5 / 23.  Up to three rounds of 128 rows still
+// pay where a workgroup's staging is small beside its sums (140 .. 190 blocks, 512
+// rows' time over 128 rows': L = 1 0.87, L = 2, r = 1 1.10 at the full rate, 0.91 at the
+// block rate; L = 4 1.26 .. 1.57 and 1.00 .. 1.09; L = 8 1.12 .. 1.49 and 1.21 .. 1.34), a
+// fourth only at the full rate from r = 4 (200 .. 250 blocks: 1.02 .. 1.23, others 0.67
+// .. 1.01).
+int corr_small_rows(int64_t nrows, int L, int r, int block)
+{
+    if (cdiv(nrows, 64) <= 256) return 64;
+    const int64_t wg128 = cdiv(nrows, 128);
+    if (wg128 <= 512) return 128;
+    if (wg128 <= 768 && (L >= 4 || (L >= 2 && !block))) return 128;
+    return wg128 < 1024 && !block && r >= 4 ? 128 : 512;
+}
 
 int corr_rows_per_tile() { return kTA; }
 int corr_small_max_L() { return kSmallMaxL; }

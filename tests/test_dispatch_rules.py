@@ -36,3 +36,26 @@ SPLIT128, FP32_64 = 17, 5
 def test_fp32_tile(rule, P, Q, nkb, cfg):
     f = rule("_ZN2pj19gemm_default_configEilll", ctypes.c_int, ctypes.c_int, *[ctypes.c_long] * 3)
     assert f(F32, P, Q, nkb) == cfg
+
+
+FULL, BLOCK = 0, 1
+
+
+@pytest.mark.parametrize("blocks,L,r,rate,rows", [
+    (8, 1, 1, FULL, 64), (32, 2, 1, BLOCK, 64), (40, 1, 1, FULL, 128), (40, 8, 4, FULL, 128), (49, 2, 1, BLOCK, 128),
+    (100, 1, 1, FULL, 128), (128, 1, 1, BLOCK, 128), (160, 1, 1, FULL, 512), (160, 2, 1, BLOCK, 512),
+    (160, 2, 1, FULL, 128), (160, 4, 1, BLOCK, 128), (160, 8, 8, FULL, 128), (250, 1, 1, FULL, 512),
+    (250, 2, 2, FULL, 512), (250, 4, 4, FULL, 128), (250, 4, 4, BLOCK, 512), (250, 8, 1, FULL, 512),
+    (257, 8, 8, FULL, 512), (8192, 2, 1, BLOCK, 512)])
+def test_short_block_rows(rule, blocks, L, r, rate, rows):
+    f = rule("_ZN2pj15corr_small_rowsEliii", ctypes.c_int, ctypes.c_long, *[ctypes.c_int] * 3)
+    assert f(512 * blocks, L, r, rate) == rows
+
+
+def test_short_block_rounds(rule):
+    """No cut leaves a second round of 64-row workgroups or a third of 128-row
+    ones (L = 1)."""
+    f = rule("_ZN2pj15corr_small_rowsEliii", ctypes.c_int, ctypes.c_long, *[ctypes.c_int] * 3)
+    for rows in range(1, 300 * 512, 97):
+        cut = f(rows, 1, 1, FULL)
+        assert cut == 512 or -(-rows // cut) <= (256 if cut == 64 else 512), rows
