@@ -14,13 +14,15 @@ namespace {
 // true); out[j, e] = X[j, e] - mean[e].  One thread per element e of an image
 // (consecutive threads: consecutive elements, so every image row is read
 // coalesced); the J values of a thread are summed in image order.  The images
-// go by kCenterStep at a time, all their loads in flight together; up to
-// kCenterHold images stay in registers between the sum and the subtraction,
-// more are read again (from the cache).  75 images of 288 x 288, bound by HBM
-// (50 MB): 40 us with one load in flight per thread, 13.5 us.
-constexpr int kCenterStep = 16, kCenterHold = 96;
+// go by S at a time, all their loads in flight together; with HOLD they all
+// (J <= S, at most kCenterHold) stay in registers between the sum and the
+// subtraction, else they are read again (from the cache).  S follows J: loads
+// past the last image cost as much as the others (1 image of 288 x 288 as one of 96:
+// 8.3 us, as one of 2: 1.9 us; 10 images: 8.8, as 24 3.6 us).  75 images of 288 x 288,
+// bound by HBM (50 MB): 37 us with one load in flight per thread, 12 us.
+constexpr int kCenterHold = 96;
 
-template <bool GIVEN, bool HOLD>
+template <bool GIVEN, bool HOLD, int S>
 __global__ __launch_bounds__(64) void center_kernel(int J, int64_t mn, const float* __restrict__ X,
                                                     float* __restrict__ mean, float* __restrict__ out)
 {
@@ -28,7 +30,6 @@ __global__ __launch_bounds__(64) void center_kernel(int J, int64_t mn, const flo
     if (e >= mn) return;
     X += e;
     out += e;
-    constexpr int S = HOLD ? kCenterHold : kCenterStep;
     float x[S];
     // images j0 .. j0 + S - 1; past the last the last one again, unused
     auto load = [&](int j0) {
@@ -99,12 +100,20 @@ int launch_center(int J, int64_t mn, const float* X, float* mean, float* out, bo
 {
     if (cdiv(mn, 64) > 0x7fffffff) return -2;
     const dim3 grid((unsigned)cdiv(mn, 64));
-    if (given)
-        hipLaunchKernelGGL((center_kernel<true, false>), grid, dim3(64), 0, s, J, mn, X, mean, out);
-    else if (J <= kCenterHold)
-        hipLaunchKernelGGL((center_kernel<false, true>), grid, dim3(64), 0, s, J, mn, X, mean, out);
-    else
-        hipLaunchKernelGGL((center_kernel<false, false>), grid, dim3(64), 0, s, J, mn, X, mean, out);
+#define PJ_CENTER(GIVEN_, HOLD_, S_) \
+    hipLaunchKernelGGL((center_kernel<GIVEN_, HOLD_, S_>), grid, dim3(64), 0, s, J, mn, X, mean, out)
+    if (given) {
+        if (J <= 2) PJ_CENTER(true, false, 2);
+        else if (J <= 8) PJ_CENTER(true, false, 8);
+        else PJ_CENTER(true, false, 16);
+    }
+    else if (J <= 2) PJ_CENTER(false, true, 2);
+    else if (J <= 8) PJ_CENTER(false, true, 8);
+    else if (J <= 24) PJ_CENTER(false, true, 24);
+    else if (J <= 48) PJ_CENTER(false, true, 48);
+    else if (J <= kCenterHold) PJ_CENTER(false, true, kCenterHold);
+    else PJ_CENTER(false, false, 16);
+#undef PJ_CENTER
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
