@@ -833,6 +833,8 @@ BwdPlan plan_bwd(int M, int W, int K, int L, int r, int prec, int64_t Gp, bool p
     const int KB = layout_of(prec).KB;
     gemm_parts_plan(prec, M, p.rg, 4 * pack_geom(1, W, 4, 4, prec).Gp / KB, &p.cfg_a, &p.parts_a);
     gemm_parts_plan(prec, p.rg, W, 4 * pack_geom(1, M, 4, 4, prec).Gp / KB, &p.cfg_b, &p.parts_b);
+    // ranges are of use to the kernels for few projections, and to FP32
+    if (r > 16 && prec != PJ_F32) p.parts_a = p.parts_b = 1, p.cfg_a = p.cfg_b = -1;
     p.dahat = off; off += align256((size_t)p.parts_a * M * p.rg * p.T);
     p.dbhat = off; off += align256((size_t)p.parts_b * p.rg * W * p.T);
     p.total = off;
@@ -871,14 +873,18 @@ int run_bwd(pj_basis b, int r, char transA, char transB, int M, int W, int K, co
         u.coef = I4; u.out = dst; u.geom = pack_geom(rows, Kc, 4, 4, prec);
         return u;
     };
-    // P x Q product over Kc into `parts` partials of P x Q (row stride Q)
-    auto gemm = [&](const void* X, int64_t P, const void* Y, int64_t Q, int64_t Kc, void* R, int cfg, int parts) {
+    // P x Q product over Kc into R (row stride Q), as `parts` partials for a
+    // synthesis that adds them (`few`); returns their number in `parts`
+    auto gemm = [&](const void* X, int64_t P, const void* Y, int64_t Q, int64_t Kc, void* R, int cfg, int& parts,
+                    bool few) {
+        if (!few && prec != PJ_F32) cfg = -1, parts = 1;
         GemmArgs g;
         g.X = X; g.gx = pack_geom(P, Kc, 4, 4, prec);
         g.Y = Y; g.gy = pack_geom(Q, Kc, 4, 4, prec);
         g.nkb = 4 * g.gx.Gp / layout_of(prec).KB;
         g.P = P; g.Q = Q; g.R = R; g.ldr = Q; g.beta = 0.0f;
-        g.nsplit = parts; g.part = parts > 1 ? R : nullptr; g.part_only = true;
+        g.nsplit = parts; g.part = parts > 1 ? R : nullptr; g.part_only = few;
+        if (!few) parts = 1;
         return launch_gemm(prec, g, cfg, st);
     };
     // the unprojected operands are only re-laid out (natural contraction
@@ -910,24 +916,30 @@ int run_bwd(pj_basis b, int r, char transA, char transB, int M, int W, int K, co
     }
     if (dA) {
         // 2. dA_hat = dR B_hat: contraction over the W columns of R
-        if (gemm(p1, M, p2, pl.rg, W, w + pl.dahat, pl.cfg_a, pl.parts_a) != 0) return PJ_ERR_HIP;
+        int parts = pl.parts_a;
+        const int ot = is_t(transA) ? 1 : 0;
+        if (gemm(p1, M, p2, pl.rg, W, w + pl.dahat, pl.cfg_a, parts, expand_few(f64, b->L, r, 0, ot)) != 0)
+            return PJ_ERR_HIP;
         // 3. dA = dA_hat spread back over each group with C
         ExpandArgs e;
         e.in = w + pl.dahat; e.ldi = pl.rg; e.in_trans = 0;
-        e.nparts = pl.parts_a; e.part = (int64_t)M * pl.rg;
-        e.out = dA; e.ldo = ldda; e.out_trans = is_t(transA) ? 1 : 0;
+        e.nparts = parts; e.part = (int64_t)M * pl.rg;
+        e.out = dA; e.ldo = ldda; e.out_trans = ot;
         e.P = M; e.K = K; e.L = b->L; e.r = r; e.Gp = pl.Gp;
         e.coef = f64 ? (const void*)b->Cd : (const void*)b->Cf;
         if (launch_expand(f64, e, st) != 0) return PJ_ERR_HIP;
     }
     if (dB) {
         // 4. dB_hat = A_hat^T dR: contraction over the M rows of R
-        if (gemm(p3, pl.rg, p4, W, M, w + pl.dbhat, pl.cfg_b, pl.parts_b) != 0) return PJ_ERR_HIP;
+        int parts = pl.parts_b;
+        const int ot = is_n(transB) ? 1 : 0;
+        if (gemm(p3, pl.rg, p4, W, M, w + pl.dbhat, pl.cfg_b, parts, expand_few(f64, b->L, r, 1, ot)) != 0)
+            return PJ_ERR_HIP;
         // 5. dB = dB_hat spread back over each group with D
         ExpandArgs e;
         e.in = w + pl.dbhat; e.ldi = W; e.in_trans = 1;
-        e.nparts = pl.parts_b; e.part = pl.rg * W;
-        e.out = dB; e.ldo = lddb; e.out_trans = is_n(transB) ? 1 : 0;
+        e.nparts = parts; e.part = pl.rg * W;
+        e.out = dB; e.ldo = lddb; e.out_trans = ot;
         e.P = W; e.K = K; e.L = b->L; e.r = r; e.Gp = pl.Gp;
         e.coef = f64 ? (const void*)b->DTd : (const void*)b->DTf;
         if (launch_expand(f64, e, st) != 0) return PJ_ERR_HIP;

@@ -9,9 +9,11 @@
 //
 // One thread per (p, group j) writes the L outputs of its group, 16 at a time:
 // for each projection l it loads in(p, l*Gp + j) once and adds it, times the
-// 16 coefficients coef[t0 .. t0 + 15, l], to 16 accumulators; the workgroup
-// stages those coefficients transposed in LDS, so they arrive as 16-byte
-// broadcast reads.  The thread index runs along p when the output is stored
+// 16 coefficients coef[t0 .. t0 + 15, l], to 16 accumulators; the loads of
+// kExpandAhead projections are in flight together (one at a time, whole backward:
+// 4096 x 4096 x 4096, L = r = 64, BF16 573 us, 478 us; L = 64, r = 32 313 and 266 us), and
+// the workgroup stages the coefficients transposed in LDS, so they arrive as
+// 16-byte broadcast reads.  The thread index runs along p when the output is stored
 // with p contiguous (each output is then one coalesced store per wave) and
 // along (p, j), j fastest, otherwise (the workgroup then parks its groups'
 // runs in LDS and 16 consecutive lanes write each run).
@@ -23,6 +25,26 @@ namespace {
 
 constexpr int kExpandChunk = 16;          // outputs of a group per pass
 constexpr int kExpandMaxR = 256;
+constexpr int kExpandAhead = 8;           // projections whose loads are in flight together (divides kExpandMaxR)
+
+// in(p, kk) of RC projections l = 0 .. RC - 1 (zero from r up), the partials
+// added last first; all loads of a partial in flight together.
+template <typename T, int RC>
+__device__ __forceinline__ void load_projected(const T* __restrict__ src, int64_t step, int r, int nparts,
+                                               int64_t part, T (&v)[RC])
+{
+#pragma unroll
+    for (int l = 0; l < RC; ++l) v[l] = src[(nparts - 1) * part + (l < r ? l : 0) * step];
+    for (int q = nparts - 2; q >= 0; --q) {
+        T u[RC];
+#pragma unroll
+        for (int l = 0; l < RC; ++l) u[l] = src[q * part + (l < r ? l : 0) * step];
+#pragma unroll
+        for (int l = 0; l < RC; ++l) v[l] += u[l];
+    }
+#pragma unroll
+    for (int l = 0; l < RC; ++l) v[l] = l < r ? v[l] : T(0);
+}
 
 template <typename T, bool OUT_T>
 __global__ __launch_bounds__(256) void expand_kernel(const T* __restrict__ in, int64_t ldi, int in_trans,
@@ -45,26 +67,30 @@ __global__ __launch_bounds__(256) void expand_kernel(const T* __restrict__ in, i
     }
     const bool live = p < P && j < G;
     const int tlim = live ? (int)((K - j * L) < L ? (K - j * L) : L) : 0;   // the last group may be partial
+    const int64_t step = in_trans ? Gp * ldi : Gp;                          // from one projection to the next
+    const T* src = in + (in_trans ? j * ldi + p : p * ldi + j);
+    const int rc = (r + kExpandAhead - 1) / kExpandAhead * kExpandAhead;    // coefficients past r are zero
     // the chunk loop runs over [0, L) for every thread (it holds barriers)
     for (int t0 = 0; t0 < L; t0 += kExpandChunk) {
         __syncthreads();
-        for (int x = threadIdx.x; x < r * kExpandChunk; x += 256) {
+        for (int x = threadIdx.x; x < rc * kExpandChunk; x += 256) {
             const int l = x / kExpandChunk, e = x - l * kExpandChunk;
-            cs[x] = t0 + e < L ? coef[(int64_t)(t0 + e) * L + l] : T(0);
+            cs[x] = t0 + e < L && l < r ? coef[(int64_t)(t0 + e) * L + l] : T(0);
         }
         __syncthreads();
         T acc[kExpandChunk];
 #pragma unroll
         for (int e = 0; e < kExpandChunk; ++e) acc[e] = T(0);
         if (t0 < tlim)
-            for (int l = 0; l < r; ++l) {
-                const int64_t kk = (int64_t)l * Gp + j;
-                const T* src = in + (in_trans ? kk * ldi + p : p * ldi + kk);
-                T v = src[(nparts - 1) * part];
-                for (int q = nparts - 2; q >= 0; --q) v += src[q * part];
-                const T* c = cs + l * kExpandChunk;
+            for (int l0 = 0; l0 < r; l0 += kExpandAhead) {
+                T v[kExpandAhead];
+                load_projected<T, kExpandAhead>(src + l0 * step, step, r - l0, nparts, part, v);
 #pragma unroll
-                for (int e = 0; e < kExpandChunk; ++e) acc[e] += v * c[e];
+                for (int i = 0; i < kExpandAhead; ++i) {
+                    const T* c = cs + (l0 + i) * kExpandChunk;
+#pragma unroll
+                    for (int e = 0; e < kExpandChunk; ++e) acc[e] += v[i] * c[e];
+                }
             }
         if (OUT_T) {
             const int64_t k0 = j * L + t0;
@@ -91,25 +117,6 @@ __global__ __launch_bounds__(256) void expand_kernel(const T* __restrict__ in, i
     }
 }
 
-// in(p, kk) of RC projections l = 0 .. RC - 1 (zero from r up), the partials
-// added last first; all loads of a partial in flight together.
-template <int RC>
-__device__ __forceinline__ void load_projected(const float* __restrict__ src, int64_t step, int r, int nparts,
-                                               int64_t part, float (&v)[RC])
-{
-#pragma unroll
-    for (int l = 0; l < RC; ++l) v[l] = src[(nparts - 1) * part + (l < r ? l : 0) * step];
-    for (int q = nparts - 2; q >= 0; --q) {
-        float u[RC];
-#pragma unroll
-        for (int l = 0; l < RC; ++l) u[l] = src[q * part + (l < r ? l : 0) * step];
-#pragma unroll
-        for (int l = 0; l < RC; ++l) v[l] += u[l];
-    }
-#pragma unroll
-    for (int l = 0; l < RC; ++l) v[l] = l < r ? v[l] : 0.0f;
-}
-
 // Few projections, FP32.  Row-major output and input, L a multiple of 4: a
 // thread owns 4 consecutive indices t of a group (the same in every group it
 // visits, so its 4 x RC coefficients stay in registers), L / 4 threads a group,
@@ -117,14 +124,15 @@ __device__ __forceinline__ void load_projected(const float* __restrict__ src, in
 // of kExRows rows and kExGroups groups in LDS, [row][l][group].  Bound by HBM
 // (the output): 4096 x 4096, L = 64, r = 8 (67 MB written): 33.6 us with 64-byte
 // runs through LDS, 28 us from four partials of the projected gradient (33 us with its
-// loads one after another).
+// loads one after another).  Rows that are not 16-byte aligned are stored value by
+// value (whole backward, 512 x 4093, L = 64, r = 16: 169 us in the general kernel, 77).
 constexpr int kExRows = 4, kExGroups = 64;
 
 template <int RC>
 __global__ __launch_bounds__(256) void expand_rows_kernel(const float* __restrict__ in, int64_t ldi,
                                                           float* __restrict__ out, int64_t ldo, int64_t P, int64_t K,
                                                           int L, int r, int64_t Gp, const float* __restrict__ coef,
-                                                          int nparts, int64_t part)
+                                                          int nparts, int64_t part, int vec)
 {
     static_assert(kExRows * kExGroups == 256, "one thread a row and group");
     __shared__ float xs[kExRows][RC][kExGroups];
@@ -137,7 +145,7 @@ __global__ __launch_bounds__(256) void expand_rows_kernel(const float* __restric
         const int j = threadIdx.x % kExGroups, row = threadIdx.x / kExGroups;
         float v[RC];
         const int64_t p = p0 + row < P ? p0 + row : P - 1;
-        load_projected<RC>(in + p * ldi + j0 + (j < ng ? j : 0), Gp, r, nparts, part, v);
+        load_projected<float, RC>(in + p * ldi + j0 + (j < ng ? j : 0), Gp, r, nparts, part, v);
 #pragma unroll
         for (int l = 0; l < RC; ++l) xs[row][l][j] = v[l];
     }
@@ -159,7 +167,7 @@ __global__ __launch_bounds__(256) void expand_rows_kernel(const float* __restric
             }
             const int64_t k = (j0 + g) * L + t;
             float* dst = out + (p0 + row) * ldo + k;
-            if (k + 3 < K) {
+            if (vec && k + 3 < K) {
                 *reinterpret_cast<f32x4*>(dst) = acc;
             } else {
 #pragma unroll
@@ -183,7 +191,7 @@ __global__ __launch_bounds__(256) void expand_cols_kernel(const float* __restric
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t j = blockIdx.y;
     float v[RC];
-    load_projected<RC>(in + j * ldi + (p < P ? p : P - 1), Gp * ldi, r, nparts, part, v);
+    load_projected<float, RC>(in + j * ldi + (p < P ? p : P - 1), Gp * ldi, r, nparts, part, v);
     for (int x = threadIdx.x; x < L * RC; x += 256) cs[x] = coef[(x / RC) * L + (x % RC < r ? x % RC : 0)];
     __syncthreads();
     if (p >= P) return;
@@ -201,11 +209,11 @@ __global__ __launch_bounds__(256) void expand_cols_kernel(const float* __restric
 // The kernels above where they apply: 1 launched, 0 not applicable, -1 failed.
 int launch_few(const ExpandArgs& a, hipStream_t s)
 {
-    if (a.r > 16 || a.L > 256 || a.in_trans != a.out_trans) return 0;
+    if (!expand_few(0, a.L, a.r, a.in_trans, a.out_trans)) return 0;
     const int64_t G = cdiv(a.K, a.L);
-#define PJ_EXF(KERN_, RC_, GX_, GY_)                                                                              \
+#define PJ_EXF(KERN_, RC_, GX_, GY_, ...)                                                                        \
     hipLaunchKernelGGL(KERN_<RC_>, dim3((unsigned)(GX_), (unsigned)(GY_)), dim3(256), 0, s, (const float*)a.in, a.ldi, \
-                       (float*)a.out, a.ldo, a.P, a.K, a.L, a.r, a.Gp, (const float*)a.coef, a.nparts, a.part)
+                       (float*)a.out, a.ldo, a.P, a.K, a.L, a.r, a.Gp, (const float*)a.coef, a.nparts, a.part __VA_ARGS__)
     if (a.out_trans) {
         const int64_t gx = cdiv(a.P, 256);
         if (gx > 0x7fffffff || G > 65535) return 0;
@@ -213,12 +221,12 @@ int launch_few(const ExpandArgs& a, hipStream_t s)
         else if (a.r <= 8) PJ_EXF(expand_cols_kernel, 8, gx, G);
         else PJ_EXF(expand_cols_kernel, 16, gx, G);
     } else {
-        if (a.L % 4 != 0 || a.ldo % 4 != 0 || (uintptr_t)a.out % 16 != 0) return 0;
+        const int vec = a.ldo % 4 == 0 && (uintptr_t)a.out % 16 == 0;
         const int64_t gx = cdiv(a.P, kExRows), gy = cdiv(G, kExGroups);
         if (gx > 0x7fffffff || gy > 65535) return 0;
-        if (a.r <= 4) PJ_EXF(expand_rows_kernel, 4, gx, gy);
-        else if (a.r <= 8) PJ_EXF(expand_rows_kernel, 8, gx, gy);
-        else PJ_EXF(expand_rows_kernel, 16, gx, gy);
+        if (a.r <= 4) PJ_EXF(expand_rows_kernel, 4, gx, gy, , vec);
+        else if (a.r <= 8) PJ_EXF(expand_rows_kernel, 8, gx, gy, , vec);
+        else PJ_EXF(expand_rows_kernel, 16, gx, gy, , vec);
     }
 #undef PJ_EXF
     return hipGetLastError() == hipSuccess ? 1 : -1;
@@ -253,6 +261,11 @@ int launch_t(const ExpandArgs& a, hipStream_t s)
 }
 
 }  // namespace
+
+bool expand_few(int is_double, int L, int r, int in_trans, int out_trans)
+{
+    return !is_double && r <= 16 && L <= 256 && in_trans == out_trans && (out_trans || L % 4 == 0);
+}
 
 int launch_expand(int is_double, const ExpandArgs& a, hipStream_t s)
 {

@@ -1087,10 +1087,11 @@ __global__ PJ_GEMM_BOUNDS void gemm_kernel(
 }
 
 // Sum of the k-range partials, highest range (highest projections) first,
-// then beta R.
+// then beta R.  R may be the first partial itself (ldr = Q): a thread reads and
+// writes one element.
 template <typename OT>
-__global__ __launch_bounds__(256) void gemm_split_sum_kernel(const OT* __restrict__ part, int nsplit, int64_t P,
-                                                             int64_t Q, OT* __restrict__ R, int64_t ldr, float beta)
+__global__ __launch_bounds__(256) void gemm_split_sum_kernel(const OT* part, int nsplit, int64_t P, int64_t Q, OT* R,
+                                                             int64_t ldr, float beta)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= P * Q) return;
@@ -1552,7 +1553,12 @@ int gemm_split_count(int prec, int64_t P, int64_t Q, int64_t nkb, int cfg)
 // at least 32 k-blocks where those give at least half the CUs a workgroup, at
 // most 8 ranges (each is a pass over a P x Q array for the consumer).  4096 x 512
 // over 4096, BF16, as the 64 x 64 direct tiles of gemm_default_config: 44.5 us,
-// as four ranges of 64 tiles: 28.5 us, their sum inside the synthesis.
+// as four ranges of 64 tiles: 28.5 us, their sum inside the synthesis.  That is
+// for the synthesis that reads every partial once (expand_few); where it reads
+// them for every 16 outputs, the 16-bit formats do better without ranges (whole
+// backward, 256 x 4096 over 4096, L = 64, r = 32: 111 us, 129 us with them; 512 x 2048 over 2048,
+// L = r = 32: 65 and 74 us) and FP32 with ranges added up by a kernel of its own
+// (2048 x 2048 over 2048, L = 64, r = 32: 201 us, 209 us in the synthesis, 225 us without ranges).
 void gemm_parts_plan(int prec, int64_t P, int64_t Q, int64_t nkb, int* cfg, int* nparts)
 {
     *cfg = gemm_default_config(prec, P, Q, nkb);
