@@ -217,7 +217,7 @@ int pj_gemm_tile_configs(int prec, int* tile_m, int* tile_n, int max_configs);
 /* Bytes of workspace proj_gemm_backward needs (0 for invalid arguments):
  * both operands of both contractions at once (dR in two orders, A_hat, B_hat),
  * and the projected gradients, each as up to 8 partials (r <= 16, or PJ_F32;
- * at most 128 MB each).  The size is the same whichever gradients are asked for. */
+ * at most 34 MB each).  The size is the same whichever gradients are asked for. */
 size_t pj_gemm_backward_workspace_bytes(int M, int W, int K, int L, int r, int prec);
 
 /* Gradients of R = A Q_{r,K} B (the forward of proj_gemm) for the upstream

@@ -37,6 +37,8 @@
 
 namespace pj {
 
+bool pack_columns_pay(int prec, int64_t P, int64_t K, int L, int r, int aligned, int split);
+
 namespace {
 
 constexpr int kPackThreads = 256;
@@ -1043,19 +1045,18 @@ template <typename TIn, int PREC>
 int launch_p(const PackArgs* a, int n, hipStream_t s)
 {
     bool ca = col_route<TIn, PREC>(a[0]), cb = n > 1 && col_route<TIn, PREC>(a[1]);
-    // Two sides the tile packer takes in one launch, or one side alone, go by
-    // columns from 4 MB of transposed source: below that a second launch, or the
-    // pass of one thread over all L indices, costs more than the tiles do (64 x
-    // 818 on both sides: 8.0 us by tiles, 10.8 us by columns; 256 x 256 FP64, one side
-    // transposed: 7.1 us in one launch, 11.2 us in two; 2101 x 3001: 27.7 against 13.8 us).
-    // Sides that need a launch each anyway always do (296 x 128 and 128 x 173: whole
-    // call 28 -> 20 us).
     if (ca || cb) {
+        // one launch of the tile packer would take both sides
+        const bool shared = n > 1 && (std::is_same<TIn, double>::value ||
+                                      job_layout(make_job<TIn, PREC>(a[0])) == job_layout(make_job<TIn, PREC>(a[1])));
         const double bytes = (ca ? (double)a[0].P * a[0].K : 0.0) + (cb ? (double)a[1].P * a[1].K : 0.0);
-        if (bytes * sizeof(TIn) < 4e6 &&
-            (n == 1 || std::is_same<TIn, double>::value ||
-             job_layout(make_job<TIn, PREC>(a[0])) == job_layout(make_job<TIn, PREC>(a[1]))))
+        if (bytes * sizeof(TIn) < 4e6 && (n == 1 || shared)) {
             ca = cb = false;
+        } else {
+            const bool split = shared && ca != cb;       // columns for one side cost the other's launch
+            ca = ca && pack_columns_pay(PREC, a[0].P, a[0].K, a[0].L, a[0].r, make_job<TIn, PREC>(a[0]).vec4, split);
+            cb = cb && pack_columns_pay(PREC, a[1].P, a[1].K, a[1].L, a[1].r, make_job<TIn, PREC>(a[1]).vec4, split);
+        }
     }
     if (ca && (n == 1 || cb)) return launch_colpack<TIn, PREC>(a, n, s);
     if (ca || cb) {
@@ -1126,6 +1127,9 @@ __host__ __device__ constexpr int col_order(int u, int TC)
 template <int RL, int EW>
 constexpr int col_depth() { return RL * EW <= 32 ? 4 : 2; }
 
+// One row of zeros of a column tile.
+static __device__ const __align__(16) char kZeroRow[kColW * sizeof(double)] = {};
+
 template <typename TIn, int PREC, int RL, int SPLIT>
 __device__ __forceinline__ void colpack_tile(const ColJob<TIn>& J, int64_t tix)
 {
@@ -1173,33 +1177,36 @@ __device__ __forceinline__ void colpack_tile(const ColJob<TIn>& J, int64_t tix)
 #pragma unroll
                 for (int q = 0; q < RL; ++q) acc[q][e] += c[q] * x[e];
         };
-        // groups inside the source; padding groups (past K) stay zero
-        if (k0 >= J.K) {
-        } else if (k0 + (int64_t)EW * L <= J.K && L >= D) {
+        // D indices in flight, none past L.  With rows past K (`ragged`) a load
+        // chooses its row, those take a row of zeros.
+        auto sum = [&](auto ragged) {
             const char* row = reinterpret_cast<const char*>(base + k0 * J.ld);
             const int64_t step = J.ld * (int64_t)sizeof(TIn), estep = step * L;
+            const int left = (int)(J.K - k0 < (int64_t)EW * L ? J.K - k0 : (int64_t)EW * L);   // rows from k0
             int u0 = 0, u = 0;                   // next place of the sums: round and place in it
             auto ld = [&](TIn (&x)[EW]) {
                 const char* q = row;
+                int t = u0;
                 if (TC > 0) {
-                    q += (int64_t)(u0 + col_order(u, TC)) * step;
+                    t += col_order(u, TC);
+                    q += (int64_t)t * step;
                     if (++u == TC) {
                         u0 += TC;
                         u = 0;
                     }
                 } else {
                     row += step;
+                    ++u0;
                 }
 #pragma unroll
-                for (int e = 0; e < EW; ++e, q += estep) {
-                    uintptr_t a = (uintptr_t)q;
+                for (int e = 0; e < EW; ++e, q += estep, t += L) {
+                    uintptr_t a = (uintptr_t)(!ragged || t < left ? q : kZeroRow);
                     asm volatile("" : "+s"(a));
                     using GB = const __attribute__((address_space(1))) char;
                     using GT = const __attribute__((address_space(1))) TIn;
                     x[e] = *(GT*)((GB*)a + col);
                 }
             };
-            // D indices in flight, none past L
             TIn x[D][EW];
 #pragma unroll
             for (int d = 0; d < D; ++d) ld(x[d]);
@@ -1219,9 +1226,11 @@ __device__ __forceinline__ void colpack_tile(const ColJob<TIn>& J, int64_t tix)
 #pragma unroll
             for (int d = 0; d + 1 < D; ++d)
                 if (t + D + d < L) fma(t + D + d, x[d]);
-        } else {
-            for (int i = 0; i < L; ++i) {
-                const int t = TC > 0 ? i / TC * TC + col_order(i % TC, TC) : i;
+        };
+        // groups inside the source; padding groups (past K) stay zero
+        if (k0 >= J.K) {
+        } else if (L < D) {                      // TC = 0
+            for (int t = 0; t < L; ++t) {
                 TIn x[EW];
 #pragma unroll
                 for (int e = 0; e < EW; ++e) {
@@ -1230,8 +1239,12 @@ __device__ __forceinline__ void colpack_tile(const ColJob<TIn>& J, int64_t tix)
                     const TIn v = *reinterpret_cast<const TIn*>(q + col);
                     x[e] = k < J.K ? v : (TIn)0;
                 }
-                fma(i, x);
+                fma(t, x);
             }
+        } else if (k0 + (int64_t)EW * L <= J.K) {
+            sum(std::false_type{});
+        } else {
+            sum(std::true_type{});
         }
         auto put = [&](int q, const TIn (&v)[E]) {
             const int l = l0 + q;
@@ -1644,6 +1657,57 @@ int launch_repack_t(const PackArgs* a, int n, hipStream_t s)
 }
 
 }  // namespace
+
+// Whether a transposed source of P rows goes column by column rather than
+// through the tile packer (from 4 MB, or where each side has a launch of its own
+// in any case: 64 x 818 on both sides 8.0 us by tiles, 10.8 by columns; 296 x 128 and
+// 128 x 173: whole call 28 -> 20 us).  `aligned`: its rows can be loaded 16 bytes at a time;
+// `split`: the tile packer would take the other side in the same launch, columns
+// cost it one.  us, tiles against columns:
+//   rows not aligned: the tile packer loads single values.  Columns always (4096 x
+//     4097, L = 32, r = 32 102 against 40; 8192 x 101, L = 256, r = 64 569 against 186).
+//   L <= 16 or r = 1, FP32 input: columns (4096 x 4096, L = 8, r = 4 92 against 18; L = 16,
+//     r = 16 51 against 24; 512 x 256, L = 16, r = 16 5.8 against 5.5; 1472 x 2048, L = 64, r = 1
+//     9.4 against 6.2).
+//   longer groups, FP32 input: a workgroup's sums are a chain of L indices, once per
+//     16 projections, so the columns need enough workgroups of 64 to hide it
+//     (`wgs`): FP32, L = 64, r = 8, 1024 workgroups (4096 x 4096) 27.4 against 23.5, 744
+//     26.6 against 21.5, 512 (4096 x 2048) 13.5 against 16.4, 64 9.3 against 11.8; r = 64,
+//     1024: 84.8 against 87.9, 1472: 75.8 against 58; L = 256, 512: 40 against 63.  The tiles
+//     of the 16-bit formats, and of an L that is no power of two, are slower and
+//     break even earlier (BF16, L = 64, r = 8, 32 workgroups 14.6 against 14.3; r = 16, 256:
+//     19.7 against 19.2, 128: 15.3 against 18.1; FP32, L = 48, r = 2, 539: 23.3 against 16.6).
+//   FP64: columns, but for passes of 64 projections that are nearly full (L = r = 64,
+//     1024 x 1024 34.9 against 37.8; r = 33 33.1 against 28.1).
+//   split, one launch against two: pays once the pair's tiles fill the chip more
+//     than once (FP64, both 1024 x 1024, L = 16, r = 4, 512 workgroups a side 11.6 against
+//     10.3; L = 32, r = 16, 256: 10.7 against 15.6; 2048 x 2048, L = 256, r = 200, 64: 996 against
+//     1468; FP32, both 1024 x 1024, L = 12, r = 5, 352: 11.2 against 14.2; 4096 x 4096, 5504: 119
+//     against 80).
+bool pack_columns_pay(int prec, int64_t P, int64_t K, int L, int r, int aligned, int split)
+{
+    const Layout ly = layout_of(prec);
+    const int64_t G = cdiv(K, L);
+    const int64_t tiles = cdiv(P, ly.RB) * cdiv(G, ly.KB);               // the tile packer's workgroups
+    const double mb = 1e-6 * (double)P * (double)K * (prec == P_F64 ? 8 : 4);
+    if (prec == P_F64) {
+        if (split) return tiles >= (r > 16 ? 250 : aligned ? 480 : 0);
+        return !(aligned && r >= 48 && r <= 64 && mb < 16.0);
+    }
+    if (!aligned) return true;
+    const bool b16 = ly.E == 8, pow2 = (L & (L - 1)) == 0;
+    if (split && tiles < (L <= 32 ? 1000 : 2000) / (b16 ? 2 : 1)) return false;
+    if (L <= 16 || r == 1) return true;
+    const double wgs = (double)cdiv(P, 64) * (double)G / ly.E;
+    int64_t need;
+    if (b16 && r <= 8) need = pow2 && L > 128 ? 64 : 0;
+    else if (b16) need = !pow2 ? (L <= 32 ? 128 : 256) : L <= 32 ? 256 : L <= 128 ? 192 : INT64_MAX;
+    else if (!pow2) need = (r <= 4 ? 8 : r > 16 ? 48 : L <= 32 ? 16 : 24) * L;
+    else if (L == 32) need = r <= 8 ? 512 : r <= 16 ? 768 : 1024;
+    else if (L == 64) need = r <= 16 ? 640 : 1200;
+    else need = (r <= 16 ? 8 : 32) * L;
+    return wgs >= (double)need;
+}
 
 int launch_repack_n(int prec, const PackArgs* a, int n, hipStream_t s)
 {

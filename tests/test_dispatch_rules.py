@@ -59,3 +59,21 @@ def test_short_block_rounds(rule):
     for rows in range(1, 300 * 512, 97):
         cut = f(rows, 1, 1, FULL)
         assert cut == 512 or -(-rows // cut) <= (256 if cut == 64 else 512), rows
+
+
+@pytest.mark.parametrize("prec,P,K,L,r,aligned,split,columns", [
+    (F32, 4097, 4096, 32, 32, 0, 0, 1), (F32, 101, 8192, 256, 64, 0, 0, 1), (BF16, 257, 4096, 64, 64, 0, 0, 1),
+    (F32, 4096, 4096, 8, 4, 1, 0, 1), (F32, 1000, 2048, 16, 16, 1, 0, 1), (F32, 4096, 4096, 64, 8, 1, 0, 1),
+    (F32, 4096, 4096, 64, 16, 1, 0, 1), (F32, 4096, 4096, 64, 64, 1, 0, 0), (F32, 2048, 4096, 64, 8, 1, 0, 0),
+    (F32, 256, 4096, 64, 8, 1, 0, 0), (F32, 1024, 1024, 64, 64, 1, 0, 0), (F32, 128, 8192, 64, 16, 1, 0, 0),
+    (F32, 4096, 4096, 256, 16, 1, 0, 0), (F32, 4096, 4096, 256, 256, 1, 0, 0), (F32, 4096, 4096, 32, 32, 1, 0, 1),
+    (F32, 1000, 2048, 32, 16, 1, 0, 0), (F32, 4096, 4096, 48, 20, 1, 0, 0), (F32, 64, 65536, 32, 8, 1, 0, 0),
+    (BF16, 256, 4096, 64, 8, 1, 0, 1), (BF16, 256, 4096, 64, 16, 1, 0, 0), (BF16, 4096, 4096, 64, 64, 1, 0, 1),
+    (BF16, 4096, 4096, 256, 16, 1, 0, 0), (BF16, 32, 65536, 64, 16, 1, 0, 0), (BF16, 4096, 4096, 32, 32, 1, 0, 1),
+    (F64, 1024, 1024, 64, 33, 1, 0, 1), (F64, 1024, 1024, 64, 64, 1, 0, 0), (F64, 2048, 2048, 64, 64, 1, 0, 1),
+    (F64, 1024, 1024, 16, 4, 1, 1, 1), (F64, 1024, 1024, 32, 16, 1, 1, 0), (F64, 2048, 2048, 256, 200, 1, 1, 0),
+    (F64, 1000, 2048, 64, 17, 1, 1, 1), (F32, 1024, 1024, 12, 5, 1, 1, 0), (F32, 4096, 4096, 12, 5, 1, 1, 1),
+    (F32, 4096, 4096, 48, 6, 1, 1, 0)])
+def test_pack_columns(rule, prec, P, K, L, r, aligned, split, columns):
+    f = rule("_ZN2pj16pack_columns_payEilliiii", ctypes.c_bool, ctypes.c_int, *[ctypes.c_long] * 2, *[ctypes.c_int] * 4)
+    assert f(prec, P, K, L, r, aligned, split) == bool(columns)
