@@ -1248,11 +1248,14 @@ __device__ __forceinline__ void colpack_tile(const ColJob<TIn>& J, int64_t tix)
         }
         auto put = [&](int q, const TIn (&v)[E]) {
             const int l = l0 + q;
-            if (l >= r || !live) return;
+            if (l >= r || p >= (J.P + RB - 1) / RB * RB) return;
+            TIn w[E];                                        // the last row block's rows past P are zero
+#pragma unroll
+            for (int e = 0; e < E; ++e) w[e] = live ? v[e] : (TIn)0;
             const int64_t kb = ((int64_t)l * J.Gp + j0) / KB;
             const int64_t off = ((p / RB * J.nkb + kb) * 64 + g0 / E * RB + p % RB) * (int64_t)ly.LB;
-            store_lane<PREC, E, TIn>(J.out, off, J.plane_stride, 0, v);
-            if (J.keep) {
+            store_lane<PREC, E, TIn>(J.out, off, J.plane_stride, 0, w);
+            if (J.keep && live) {
                 TIn* dst = J.keep + p * J.keep_ld + (int64_t)l * J.Gp + j0 + g0;
 #pragma unroll
                 for (int e = 0; e < E; ++e) dst[e] = v[e];
