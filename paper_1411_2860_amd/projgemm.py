@@ -540,11 +540,13 @@ class GemmDesc(ctypes.Structure):
 def _descs(As, Bs, Rs, transA=False, transB=False):
     n = len(As)
     arr = (GemmDesc * n)()
+    tA, tB = b"T" if transA else b"N", b"T" if transB else b"N"
     for i, (A, B, R) in enumerate(zip(As, Bs, Rs)):
-        M, K = (A.shape[1], A.shape[0]) if transA else tuple(A.shape)
-        W = B.shape[0] if transB else B.shape[1]
-        arr[i] = GemmDesc(M, W, K, b"T" if transA else b"N", b"T" if transB else b"N", _ptr(A), A.stride(0),
-                          _ptr(B), B.stride(0), _ptr(R), R.stride(0))
+        M, K = A.shape
+        if transA:
+            M, K = K, M
+        arr[i] = GemmDesc(M, B.shape[0 if transB else 1], K, tA, tB, A.data_ptr(), A.stride(0), B.data_ptr(),
+                          B.stride(0), R.data_ptr(), R.stride(0))
     return arr
 
 
@@ -570,14 +572,18 @@ def gemm_batched(As, Bs, r: int, basis: Basis, prec="bf16", transA=False, transB
     """R_i = A_i Q_{r,K_i} B_i for every problem i, in grouped pack launches
     (one per operand staging mode) and one persistent GEMM launch.  `small`
     (one flag per problem) picks each problem's tile: the configuration's, or
-    its small one; None lets the library choose.  Returns the outputs."""
+    its small one; None lets the library choose.  Returns the outputs (float64
+    for 'f64', else float32, as the operands)."""
     import torch
+    dt = torch.float64 if _prec(prec) == PREC["f64"] else torch.float32
+    if any(t.dtype != dt for t in (*As, *Bs, *(outs or ()))):
+        raise TypeError(f"operands and outputs must be {dt}")
     if outs is None:
         outs = []
         for A, B in zip(As, Bs):
             M = A.shape[1] if transA else A.shape[0]
             W = B.shape[0] if transB else B.shape[1]
-            outs.append(torch.empty((M, W), dtype=torch.float32, device=A.device))
+            outs.append(torch.empty((M, W), dtype=dt, device=A.device))
     descs = _descs(As, Bs, outs, transA, transB)
     need = gemm_batched_workspace_bytes(descs, basis.L, r, prec, tile_cfg, small)
     if need == 0:
@@ -604,6 +610,9 @@ def gemm_backward(A, B, dR, r: int, basis: Basis, prec="f32", transA=False, tran
     p = _prec(prec)
     M, K = (A.shape[1], A.shape[0]) if transA else tuple(A.shape)
     W = B.shape[0] if transB else B.shape[1]
+    dt = torch.float64 if p == PREC["f64"] else torch.float32
+    if A.dtype != dt or B.dtype != dt or dR.dtype != dt:
+        raise TypeError(f"A, B and dR must be {dt}")
     dA = torch.empty_like(A) if need_dA else None
     dB = torch.empty_like(B) if need_dB else None
     if dR.stride(1) != 1:
