@@ -1705,6 +1705,7 @@ bool pack_columns_pay(int prec, int64_t P, int64_t K, int L, int r, int aligned,
     int64_t need;
     if (b16 && r <= 8) need = pow2 && L > 128 ? 64 : 0;
     else if (b16) need = !pow2 ? (L <= 32 ? 128 : 256) : L <= 32 ? 256 : L <= 128 ? 192 : INT64_MAX;
+    else if (P < 128) need = INT64_MAX;                  // 64 x 65536, L = 32, r = 8: 9.0 against 12.0
     else if (!pow2) need = (r <= 4 ? 8 : r > 16 ? 48 : L <= 32 ? 16 : 24) * L;
     else if (L == 32) need = r <= 8 ? 512 : r <= 16 ? 768 : 1024;
     else if (L == 64) need = r <= 16 ? 640 : 1200;
