@@ -243,6 +243,7 @@ __device__ __forceinline__ void gemm_tile(
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
     const int64_t rb0 = (tm * WAVES_M + wm) * WM;
     const int64_t cb0 = (tn * WAVES_N + wn) * WN;
+    if (rb0 * T::RB >= P || cb0 * T::RB >= Q) return;      // the wave stores nothing (no barrier follows)
 
     int64_t xt[WM], yt[WN];   // first tile index of each row block
 #pragma unroll

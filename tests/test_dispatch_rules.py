@@ -77,3 +77,21 @@ def test_short_block_rounds(rule):
 def test_pack_columns(rule, prec, P, K, L, r, aligned, split, columns):
     f = rule("_ZN2pj16pack_columns_payEilliiii", ctypes.c_bool, ctypes.c_int, *[ctypes.c_long] * 2, *[ctypes.c_int] * 4)
     assert f(prec, P, K, L, r, aligned, split) == bool(columns)
+
+
+@pytest.mark.parametrize("prec,default", [("bf16", 16), ("bf16x3", 16), ("f16", 16), ("f32", 17), ("f64", 0), ("fp8", 0)])
+@pytest.mark.parametrize("shapes,small", [
+    ([(1024, 1024, 1024)] * 10, False), ([(1024, 1024, 1024)] * 10 + [(32, 32, 65536)], True),
+    ([(700, 700, 700)] * 30 + [(60, 60, 60000)] * 4, True), ([(8, 4096, 4096)] * 8, True),
+    ([(4096, 4096, 4096)] * 8 + [(100, 100, 2048)] * 9, False), ([(1500, 2500, 1000)] * 24 + [(32, 32, 4096)], False)])
+def test_batch_configuration(prec, default, shapes, small):
+    """The workspace, whose item table follows the tiles, tells which configuration a
+    batch takes: 0 where its small tiles would outlast the large ones."""
+    if prec == "f32" and shapes[0][0] == 8:               # large and small tiles have the same rows
+        small = False
+    from paper_1411_2860_amd import projgemm as pg
+    descs = (pg.GemmDesc * len(shapes))(*[pg.GemmDesc(m, w, k, b"N", b"N", 256, k, 256, w, 256, w) for m, w, k in shapes])
+    auto, chosen = (pg.gemm_batched_workspace_bytes(descs, 16, 4, prec, c) for c in (-1, 0 if small else default))
+    assert auto == chosen > 0
+    if default == 16 and shapes[0][0] > 8:                # FP32's two have tiles of one size
+        assert pg.gemm_batched_workspace_bytes(descs, 16, 4, prec, default if small else 0) != auto
