@@ -1669,7 +1669,7 @@ int launch_repack_t(const PackArgs* a, int n, hipStream_t s)
 // cost it one.  us, tiles against columns:
 //   rows not aligned: the tile packer loads single values.  Columns always (4096 x
 //     4097, L = 32, r = 32 102 against 40; 8192 x 101, L = 256, r = 64 569 against 186).
-//   L <= 16 or r = 1, FP32 input: columns (4096 x 4096, L = 8, r = 4 92 against 18; L = 16,
+//   L <= 16 or r = 1: columns (FP32, 4096 x 4096, L = 8, r = 4 92 against 18; L = 16,
 //     r = 16 51 against 24; 512 x 256, L = 16, r = 16 5.8 against 5.5; 1472 x 2048, L = 64, r = 1
 //     9.4 against 6.2).
 //   longer groups, FP32 input: a workgroup's sums are a chain of L indices, once per
@@ -1678,8 +1678,15 @@ int launch_repack_t(const PackArgs* a, int n, hipStream_t s)
 //     26.6 against 21.5, 512 (4096 x 2048) 13.5 against 16.4, 64 9.3 against 11.8; r = 64,
 //     1024: 84.8 against 87.9, 1472: 75.8 against 58; L = 256, 512: 40 against 63.  The tiles
 //     of the 16-bit formats, and of an L that is no power of two, are slower and
-//     break even earlier (BF16, L = 64, r = 8, 32 workgroups 14.6 against 14.3; r = 16, 256:
-//     19.7 against 19.2, 128: 15.3 against 18.1; FP32, L = 48, r = 2, 539: 23.3 against 16.6).
+//     break even earlier, above all on a source that is not in the caches (the figures
+//     so far were repeated on one that is; the lines stand between the two).  BF16,
+//     4096 x 1024, not in the caches: L = 64, r = 16 30.3 against 22.4, r = 32 41.6 against 37.6,
+//     r = 64 63.2 against 66.9; L = 128, r = 4 50.3 against 32.2, r = 16 (1024 x 4096) 34.4 against
+//     40.5; in them, with the contraction: L = 64, r = 16 34.4 against 36.5, r = 32 57.6 against
+//     60.8, r = 64 97.9 against 106.4; L = 256, r = 16 77.0 against 92.1.  FP32, not in the
+//     caches: L = 64, 4096 x 1024, r = 8 17.8 against 18.4, 4096 x 2048, r = 16 25.0 against 24.7,
+//     r = 64 53.9 against 69.1; L = 32, 4096 x 1024, r = 4 13.0 against 11.3; L = 48, r = 12 19.1
+//     against 18.9; L = 24, r = 8 21.6 against 12.1.
 //   FP64: columns, but for passes of 64 projections that are nearly full (L = r = 64,
 //     1024 x 1024 34.9 against 37.8; r = 33 33.1 against 28.1).
 //   split, one launch against two: pays once the pair's tiles fill the chip more
@@ -1703,11 +1710,13 @@ bool pack_columns_pay(int prec, int64_t P, int64_t K, int L, int r, int aligned,
     if (L <= 16 || r == 1) return true;
     const double wgs = (double)cdiv(P, 64) * (double)G / ly.E;
     int64_t need;
-    if (b16 && r <= 8) need = pow2 && L > 128 ? 64 : 0;
-    else if (b16) need = !pow2 ? (L <= 32 ? 128 : 256) : L <= 32 ? 256 : L <= 128 ? 192 : INT64_MAX;
+    if (b16 && r <= 16 && L <= 64) need = 0;
+    else if (b16 && L <= 64) need = L <= 32 ? (pow2 ? 0 : 128) : pow2 ? 192 : 256;
+    else if (b16 && L <= 128) need = r <= 8 ? 0 : 192;
+    else if (b16) need = r <= 4 ? 0 : r <= 8 ? 64 : INT64_MAX;
     else if (P < 128) need = INT64_MAX;                  // 64 x 65536, L = 32, r = 8: 9.0 against 12.0
-    else if (!pow2) need = (r <= 4 ? 8 : r > 16 ? 48 : L <= 32 ? 16 : 24) * L;
-    else if (L == 32) need = r <= 8 ? 512 : r <= 16 ? 768 : 1024;
+    else if (!pow2) need = (r <= 4 || (r <= 8 && L <= 32) ? 8 : r > 16 ? 48 : L <= 32 ? 16 : 24) * L;
+    else if (L == 32) need = r <= 4 ? 0 : r <= 8 ? 256 : r <= 16 ? 768 : 1024;
     else if (L == 64) need = r <= 16 ? 640 : 1200;
     else need = (r <= 16 ? 8 : 32) * L;
     return wgs >= (double)need;

@@ -68,8 +68,10 @@ def test_short_block_rounds(rule):
     (F32, 256, 4096, 64, 8, 1, 0, 0), (F32, 1024, 1024, 64, 64, 1, 0, 0), (F32, 128, 8192, 64, 16, 1, 0, 0),
     (F32, 4096, 4096, 256, 16, 1, 0, 0), (F32, 4096, 4096, 256, 256, 1, 0, 0), (F32, 4096, 4096, 32, 32, 1, 0, 1),
     (F32, 1000, 2048, 32, 16, 1, 0, 0), (F32, 4096, 4096, 48, 20, 1, 0, 0), (F32, 64, 65536, 32, 8, 1, 0, 0),
-    (BF16, 256, 4096, 64, 8, 1, 0, 1), (BF16, 256, 4096, 64, 16, 1, 0, 0), (BF16, 4096, 4096, 64, 64, 1, 0, 1),
-    (BF16, 4096, 4096, 256, 16, 1, 0, 0), (BF16, 32, 65536, 64, 16, 1, 0, 0), (BF16, 4096, 4096, 32, 32, 1, 0, 1),
+    (BF16, 256, 4096, 64, 8, 1, 0, 1), (BF16, 256, 4096, 64, 16, 1, 0, 1), (BF16, 1024, 4096, 64, 32, 1, 0, 0),
+    (BF16, 4096, 4096, 64, 64, 1, 0, 1),
+    (BF16, 4096, 4096, 256, 16, 1, 0, 0), (BF16, 1024, 4096, 128, 16, 1, 0, 0), (F32, 1024, 4096, 32, 4, 1, 0, 1),
+    (BF16, 4096, 4096, 32, 32, 1, 0, 1),
     (F64, 1024, 1024, 64, 33, 1, 0, 1), (F64, 1024, 1024, 64, 64, 1, 0, 0), (F64, 2048, 2048, 64, 64, 1, 0, 1),
     (F64, 1024, 1024, 16, 4, 1, 1, 1), (F64, 1024, 1024, 32, 16, 1, 1, 0), (F64, 2048, 2048, 256, 200, 1, 1, 0),
     (F64, 1000, 2048, 64, 17, 1, 1, 1), (F32, 1024, 1024, 12, 5, 1, 1, 0), (F32, 4096, 4096, 12, 5, 1, 1, 1),
