@@ -579,10 +579,16 @@ ConvFftGeom conv_fft_geom(int64_t W, int64_t N, int L, int r)
 // covering L, at least 32) after two small launches -- and of the FFT path (30 us,
 // about 0.12 ms + 0.004 ms per signal row and phase, r + L, per 2^22 samples,
 // scaled by the share of each transform that is output); the FFT path is taken
-// when it is estimated at least 20 % faster.  Its transforms have since become
-// about three times as fast as this estimate; the line stays where it was
-// because the direct sums round each output by itself, the transforms a whole
-// segment by its largest values.
+// when it is estimated at least 20 % faster.  The estimate is of earlier
+// transforms and two to three times too long now, so calls near the line run the direct
+// path although the FFT path is up to 4.5 times as fast (2^22 samples, L = 16, N = 16384,
+// r = 1: 223 against 49 us; L = 16, N = 1024, r = 16: 247 and 68; L = 32, N = 16384, r = 4: 267
+// and 53; L = 64, N = 16384, r = 8: 264 and 70).  On a stationary signal its error is
+// also the lower one (rms 1.9e-7 against 5.8e-7 for the first).  The line has not
+// been moved because a transform rounds a whole segment by its loudest part, which a
+// caller of the direct path may not expect: where four template lengths of the
+// same signal are 1e-4 times as loud, their outputs' rms error is 8e-4 to 1.2e-3 of
+// them by FFT, 2e-7 to 6e-7 direct.
 bool conv_prefers_fft(int64_t W, int64_t N, int L, int r)
 {
     const ConvFftGeom f = conv_fft_geom(W, N, L, r);

@@ -63,3 +63,25 @@ def test_no_larger_than_fp32_instructions(what, L, K, r):
 def test_single_terms(K):
     for cfg, (worst, _) in zip(CFGS, _errors("single", 1, K, 1, CFGS)):
         assert worst <= 2.1, (K, cfg, worst)
+
+
+@pytest.mark.parametrize("K", [531, 541])
+def test_long_ragged(K):
+    """1000 x 8200 outputs over 67 and 68 k-blocks, the last partly padding: both split
+    tiles and the default, every output, the columns past the last untouched."""
+    from paper_1411_2860_amd import projgemm as pg
+    from tests import _tol
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    M, W = 1000, 8200
+    A = torch.randn((M, K), generator=g, device="cuda")
+    B = torch.randn((W, K), generator=g, device="cuda")
+    ref = A.double() @ B.double().t().contiguous()
+    mag = A.double().abs() @ B.double().abs().t().contiguous()
+    Ap, Bp = pg.pack_ab(A, B, 1, pg.Basis("identity", 1), transB=True)
+    for cfg in CFGS:
+        buf = torch.full((M, W + 3), 7.0, device="cuda")
+        pg.gemm_packed(Ap, Bp, 1, M, W, K, 1, 1, 1, out=buf[:, :W], tile_cfg=cfg)
+        off = (buf[:, :W].double() - ref).abs() - _tol.gemm_bound("f32", 1, 1, -(-K // 8) * 8, mag)
+        assert bool((off <= 0).all()), (cfg, float(off.max()))
+        assert bool((buf[:, W:] == 7.0).all())
