@@ -646,8 +646,8 @@ bool prefer_small(int M, int W, int tm, int tn, int sm, int sn)
 // of workgroups, against those of the large tiles): then configuration 0, whose
 // workgroups are twice as many and small.  32 x 32 over 65536 with 10 problems of 1024 a
 // side, r = 4, BF16x3: 314 us by the default, 126 us; 4 of 60 x 60 over 60000 with 30 of 700:
-// 420 and 318 us; 8 of 8 x 4096 over 4096: 206 and 175 us; FP32, the first two: 573, 631
-// and 358, 450 us.
+// 420 and 318 us; 8 of 8 x 4096 over 4096: 206 and 175 us; FP32, the first: 573 and 358 us,
+// the second: 631 and 450 us.
 int batch_config(int count, const pj_gemm_desc* p, int L, int r, int prec)
 {
     const int cfg = gemm_grouped_default_config(prec);

@@ -1017,7 +1017,7 @@ __device__ __forceinline__ void gemm_tile_split(
 // first and its fragment reads interleaved one by one with its matrix
 // instructions (scheduling groups), so that the LDS command queue never
 // holds a whole step's reads in front of the matrix pipe, 6 = FP32 split into
-// three BF16 values (the other formats run it as kind 1).
+// three BF16 values (FP32 only).
 template <int KIND, int PREC, int WM, int WN, int WAVES_M, int WAVES_N>
 __device__ __forceinline__ void gemm_any(
     const char* __restrict__ X, int64_t x_nrb, int64_t x_nkb, int64_t x_plane, int64_t x_pb,
@@ -1349,8 +1349,8 @@ int launch_gemm_t(const GemmArgs& a, hipStream_t s)
 // blocks per wave along M, along N; waves along M, along N; minimum resident
 // workgroups per CU).  The workgroup tile is RB*WM*WAVES_M x RB*WN*WAVES_N.
 // FP8 runs the LDS kinds as direct.  FP32 runs the two kind 4 tiles (16 and 17) as
-// kind 6, three-way split operands on the BF16 instructions, in the same tiles
-// (17 on eight waves of 32 x 64 outputs): 0.7 of the time.
+// kind 6, three-way split operands on the BF16 instructions, on the same workgroup
+// tiles (17 on eight waves of 32 x 64 outputs): 0.7 of the time.
 constexpr bool split_config(int prec, int cfg) { return prec == P_F32 && (cfg == 16 || cfg == 17); }
 #define PJ_GEMM_CONFIGS(X)   \
     X(0, 0, 2, 2, 2, 2, 2)   \
