@@ -19,13 +19,15 @@
 // runs in LDS and 16 consecutive lanes write each run).
 #include "common.h"
 
+#include <type_traits>
+
 namespace pj {
 
 namespace {
 
 constexpr int kExpandChunk = 16;          // outputs of a group per pass
 constexpr int kExpandMaxR = 256;
-constexpr int kExpandAhead = 8;           // projections whose loads are in flight together (divides kExpandMaxR)
+constexpr int kExpandAhead = 8;           // projections whose loads are in flight together
 
 // in(p, kk) of RC projections l = 0 .. RC - 1 (zero from r up), the partials
 // added last first; all loads of a partial in flight together.
@@ -44,6 +46,19 @@ __device__ __forceinline__ void load_projected(const T* __restrict__ src, int64_
     }
 #pragma unroll
     for (int l = 0; l < RC; ++l) v[l] = l < r ? v[l] : T(0);
+}
+
+// acc[e] += in(p, kk) * c[l][e] of N projections.
+template <int N, typename T>
+__device__ __forceinline__ void add_projections(const T* __restrict__ src, int64_t step, int nparts, int64_t part,
+                                                const T* c, T (&acc)[kExpandChunk])
+{
+    T v[N];
+    load_projected<T, N>(src, step, N, nparts, part, v);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int e = 0; e < kExpandChunk; ++e) acc[e] += v[i] * c[i * kExpandChunk + e];
 }
 
 template <typename T, bool OUT_T>
@@ -69,29 +84,30 @@ __global__ __launch_bounds__(256) void expand_kernel(const T* __restrict__ in, i
     const int tlim = live ? (int)((K - j * L) < L ? (K - j * L) : L) : 0;   // the last group may be partial
     const int64_t step = in_trans ? Gp * ldi : Gp;                          // from one projection to the next
     const T* src = in + (in_trans ? j * ldi + p : p * ldi + j);
-    const int rc = (r + kExpandAhead - 1) / kExpandAhead * kExpandAhead;    // coefficients past r are zero
     // the chunk loop runs over [0, L) for every thread (it holds barriers)
     for (int t0 = 0; t0 < L; t0 += kExpandChunk) {
         __syncthreads();
-        for (int x = threadIdx.x; x < rc * kExpandChunk; x += 256) {
+        for (int x = threadIdx.x; x < r * kExpandChunk; x += 256) {
             const int l = x / kExpandChunk, e = x - l * kExpandChunk;
-            cs[x] = t0 + e < L && l < r ? coef[(int64_t)(t0 + e) * L + l] : T(0);
+            cs[x] = t0 + e < L ? coef[(int64_t)(t0 + e) * L + l] : T(0);
         }
         __syncthreads();
         T acc[kExpandChunk];
 #pragma unroll
         for (int e = 0; e < kExpandChunk; ++e) acc[e] = T(0);
-        if (t0 < tlim)
-            for (int l0 = 0; l0 < r; l0 += kExpandAhead) {
-                T v[kExpandAhead];
-                load_projected<T, kExpandAhead>(src + l0 * step, step, r - l0, nparts, part, v);
-#pragma unroll
-                for (int i = 0; i < kExpandAhead; ++i) {
-                    const T* c = cs + (l0 + i) * kExpandChunk;
-#pragma unroll
-                    for (int e = 0; e < kExpandChunk; ++e) acc[e] += v[i] * c[e];
-                }
-            }
+        if (t0 < tlim) {
+            int l = 0;
+            auto add = [&](auto n) {
+                add_projections<n.value>(src + l * step, step, nparts, part, cs + l * kExpandChunk, acc);
+                l += n.value;
+            };
+            while (l + kExpandAhead <= r) add(std::integral_constant<int, kExpandAhead>());
+            // the rest in powers of two: a full chunk for r = 1 took 49 us where one load takes 36
+            // (64 x 1728 over 3328, L = 4)
+            if (l + 4 <= r) add(std::integral_constant<int, 4>());
+            if (l + 2 <= r) add(std::integral_constant<int, 2>());
+            if (l < r) add(std::integral_constant<int, 1>());
+        }
         if (OUT_T) {
             const int64_t k0 = j * L + t0;
 #pragma unroll

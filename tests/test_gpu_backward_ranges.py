@@ -60,6 +60,12 @@ def test_general_synthesis(K, L, r):
     _check("f32", "dct2", 33, K, 70, L, r)
 
 
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5, 6, 7, 11, 15])
+def test_general_synthesis_rest(r):
+    """What is left of the projections after steps of 8."""
+    _check("f32", "dct2", 33, 70, 40, 15, r)
+
+
 @pytest.mark.parametrize("K,L,r", SYNTHESIS + [(40, 8, 8), (41, 8, 1)])
 def test_general_synthesis_f64(K, L, r):
     from paper_1411_2860_amd import projgemm as pg
