@@ -1053,9 +1053,22 @@ int launch_p(const PackArgs* a, int n, hipStream_t s)
         if (bytes * sizeof(TIn) < 4e6 && (n == 1 || shared)) {
             ca = cb = false;
         } else {
-            const bool split = shared && ca != cb;       // columns for one side cost the other's launch
-            ca = ca && pack_columns_pay(PREC, a[0].P, a[0].K, a[0].L, a[0].r, make_job<TIn, PREC>(a[0]).vec4, split);
-            cb = cb && pack_columns_pay(PREC, a[1].P, a[1].K, a[1].L, a[1].r, make_job<TIn, PREC>(a[1]).vec4, split);
+            const auto pays = [&](int64_t P, int64_t K, int L, int r, bool aligned, bool split) {
+                return pack_columns_pay(PREC, P, K, L, r, aligned, split);
+            };
+            const bool va = make_job<TIn, PREC>(a[0]).vec4, vb = n > 1 && make_job<TIn, PREC>(a[1]).vec4;
+            if (ca && cb) {
+                // both sides take the same packer, in one launch: by columns where the tile
+                // packer would need two (FP32, 508 and 603 rows over 4128, L = 256, r = 3 38.7 us, 78.3
+                // with the first, aligned, by tiles; 808 and 111 over 362, whole call 15.9 and 21.5), else
+                // as one source of all rows (FP32, 560 and 2240 over 2736, L = 32, r = 5 14.3 by columns, 19.1
+                // by tiles, 22.6 mixed; 2280 and 1152 over 3353, L = 32, r = 32 34.2, tiles 46.8)
+                ca = cb = !shared || pays(a[0].P + a[1].P, std::max(a[0].K, a[1].K), a[0].L, std::max(a[0].r, a[1].r),
+                                          va && vb, false);
+            } else {
+                ca = ca && pays(a[0].P, a[0].K, a[0].L, a[0].r, va, shared);     // columns for one side cost
+                cb = cb && pays(a[1].P, a[1].K, a[1].L, a[1].r, vb, shared);     // the other's launch
+            }
         }
     }
     if (ca && (n == 1 || cb)) return launch_colpack<TIn, PREC>(a, n, s);

@@ -84,3 +84,39 @@ def test_either_packer(P, K, L, r, prec):
     pg.pack_b(X, r, basis, prec=prec, out=a)
     pg.pack_b(Y, r, basis, prec=prec, out=b)          # not aligned: columns
     assert torch.equal(a, b)
+
+
+def _us(fn):
+    for _ in range(3):
+        fn()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(20):
+            fn()
+    ts = []
+    for _ in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        b.synchronize()
+        ts.append(a.elapsed_time(b) * 50)
+    return float(np.median(ts))
+
+
+@pytest.mark.parametrize("M,W,K,L,r", [(508, 603, 4128, 256, 3), (560, 2240, 2736, 32, 5), (400, 72, 2621, 32, 3)])
+def test_pair_time(M, W, K, L, r):
+    """Two transposed sources go by one packer: a column more on each (rows no longer
+    aligned: columns, one launch) moves the same bytes, 1.3 for the spread."""
+    from paper_1411_2860_amd import projgemm as pg
+    basis = pg.Basis("dct2", L)
+
+    def time(m, w):
+        A, B = torch.randn((K, m), device="cuda"), torch.randn((K, w), device="cuda")
+        oa, ob = (torch.empty(pg.packed_bytes(x, K, L, r), dtype=torch.uint8, device="cuda") for x in (m, w))
+        run = lambda: pg.pack_ab(A, B, r, basis, transA=True, out_a=oa, out_b=ob)
+        return _us(run)
+
+    t, base = time(M, W), time(M + 1, W + 1 + W % 2)
+    assert t <= 1.3 * base, (t, base)
