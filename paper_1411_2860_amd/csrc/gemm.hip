@@ -1480,13 +1480,15 @@ int gemm_default_config(int prec, int64_t P, int64_t Q, int64_t nkb)
     const int64_t tiles128 = cdiv(P, 128) * cdiv(Q, 128);
     if (prec == P_F32) {
         // The split 128 x 128 tile (17; two workgroups a CU) against the 64 x 64 one (5).
-        // Up to half a CU's worth of them, 5 has more CUs at work (4096 x 512, 512
-        // k-blocks: 150 against 156 us; 512 x 2048, 128 k-blocks: 23.9 against 42.8 us).  Where
+        // Up to two a CU of the small ones run at once, on more CUs (4096 x 512, 512
+        // k-blocks: 150 against 156 us; 512 x 2048, 128 k-blocks: 23.9 against 42.8 us; 1274 x
+        // 1561, 500 of them, 16 / 128 / 384 k-blocks 9.3 / 39 / 109 against 11.8 / 46 / 126 us; from 520
+        // (4100 x 512) 11 / 56 / 159 against 11.7 / 46 / 124 us).  Where
         // an edge leaves a quarter or more of the large tiles' area empty, 5 does
         // less work: 64 x 20000, 8 and 96 k-blocks 5.9 and 29 against 8.5 and 37 us; 129 x
         // 17000, 2 and 32 k-blocks 6.2 and 23 against 8.6 and 26 us.
         const int64_t tiles64 = cdiv(P, 64) * cdiv(Q, 64);
-        if (tiles128 <= 128 || tiles64 <= 3 * tiles128) return 5;
+        if (tiles64 <= 512 || tiles64 <= 3 * tiles128) return 5;
         // Otherwise 17 from the contraction that pays for its longer first stage:
         // up to one tile a CU by the work of 5 (1500 x 1500, 8 / 16 / 32 / 96 k-blocks: 8.4 /
         // 12.0 / 19.4 / 47 against 9.1 / 12.0 / 17.3 / 37 us; 1920 x 1920, 4 / 8: 8.1 / 10.5

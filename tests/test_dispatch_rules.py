@@ -32,7 +32,8 @@ SPLIT128, FP32_64 = 17, 5
     (96, 17000, 32, SPLIT128), (1500, 1500, 32, SPLIT128), (1920, 1920, 8, SPLIT128), (2000, 2100, 32, SPLIT128),
     (193, 17000, 32, SPLIT128), (1024, 8192, 2, SPLIT128), (1024, 8192, 128, SPLIT128), (1003, 3001, 102, SPLIT128),
     # too few tiles
-    (512, 2048, 128, FP32_64), (4096, 512, 512, FP32_64)])
+    (512, 2048, 128, FP32_64), (4096, 512, 512, FP32_64), (1274, 1561, 336, FP32_64), (1344, 1536, 16, FP32_64),
+    (4100, 512, 384, SPLIT128)])
 def test_fp32_tile(rule, P, Q, nkb, cfg):
     f = rule("_ZN2pj19gemm_default_configEilll", ctypes.c_int, ctypes.c_int, *[ctypes.c_long] * 3)
     assert f(F32, P, Q, nkb) == cfg
