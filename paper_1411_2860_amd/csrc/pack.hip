@@ -1700,6 +1700,9 @@ int launch_repack_t(const PackArgs* a, int n, hipStream_t s)
 //     caches: L = 64, 4096 x 1024, r = 8 17.8 against 18.4, 4096 x 2048, r = 16 25.0 against 24.7,
 //     r = 64 53.9 against 69.1; L = 32, 4096 x 1024, r = 4 13.0 against 11.3; L = 48, r = 12 19.1
 //     against 18.9; L = 24, r = 8 21.6 against 12.1.
+//     Below 4 MB a source is taken to be in the caches (BF16, 320 x 576, with a row-wise
+//     side: L = 64, r = 4 25.3 against 24.4, r = 16 25.7 against 29.6; L = 32, r = 16 17.4
+//     against 18.1, r = 32 29.0 against 32.1; L = 128, r = 8 41.7 against 46.4).
 //   FP64: columns, but for passes of 64 projections that are nearly full (L = r = 64,
 //     1024 x 1024 34.9 against 37.8; r = 33 33.1 against 28.1).
 //   split, one launch against two: pays once the pair's tiles fill the chip more
@@ -1721,10 +1724,11 @@ bool pack_columns_pay(int prec, int64_t P, int64_t K, int L, int r, int aligned,
     const bool b16 = ly.E == 8, pow2 = (L & (L - 1)) == 0;
     if (split && tiles < (L <= 32 ? 1000 : 2000) / (b16 ? 2 : 1)) return false;
     if (L <= 16 || r == 1) return true;
+    if (b16 && mb < 4.0 && (L > 32 ? r > (L <= 64 ? 8 : 4) : pow2 && r > 16)) return false;
     const double wgs = (double)cdiv(P, 64) * (double)G / ly.E;
     int64_t need;
     if (b16 && r <= 16 && L <= 64) need = 0;
-    else if (b16 && L <= 64) need = L <= 32 ? (pow2 ? 0 : 128) : pow2 ? 192 : 256;
+    else if (b16 && L <= 64) need = L <= 32 ? 0 : pow2 ? 192 : 128;
     else if (b16 && L <= 128) need = r <= 8 ? 0 : 192;
     else if (b16) need = r <= 4 ? 0 : r <= 8 ? 64 : INT64_MAX;
     else if (P < 128) need = INT64_MAX;                  // 64 x 65536, L = 32, r = 8: 9.0 against 12.0

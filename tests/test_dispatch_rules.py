@@ -72,6 +72,8 @@ def test_short_block_rounds(rule):
     (BF16, 256, 4096, 64, 8, 1, 0, 1), (BF16, 256, 4096, 64, 16, 1, 0, 1), (BF16, 1024, 4096, 64, 32, 1, 0, 0),
     (BF16, 4096, 4096, 64, 64, 1, 0, 1),
     (BF16, 4096, 4096, 256, 16, 1, 0, 0), (BF16, 1024, 4096, 128, 16, 1, 0, 0), (F32, 1024, 4096, 32, 4, 1, 0, 1),
+    (BF16, 192, 128, 64, 15, 1, 0, 0), (BF16, 192, 128, 64, 8, 1, 0, 1), (BF16, 576, 320, 48, 14, 1, 0, 0),
+    (BF16, 512, 512, 32, 32, 1, 0, 0), (BF16, 3352, 363, 28, 19, 1, 0, 1), (BF16, 8064, 2224, 20, 18, 1, 0, 1),
     (BF16, 4096, 4096, 32, 32, 1, 0, 1),
     (F64, 1024, 1024, 64, 33, 1, 0, 1), (F64, 1024, 1024, 64, 64, 1, 0, 0), (F64, 2048, 2048, 64, 64, 1, 0, 1),
     (F64, 1024, 1024, 16, 4, 1, 1, 1), (F64, 1024, 1024, 32, 16, 1, 1, 0), (F64, 2048, 2048, 256, 200, 1, 1, 0),
