@@ -862,7 +862,7 @@ BwdPlan plan_bwd(int M, int W, int K, int L, int r, int prec, int64_t Gp, bool p
     const int KB = layout_of(prec).KB;
     gemm_parts_plan(prec, M, p.rg, 4 * pack_geom(1, W, 4, 4, prec).Gp / KB, &p.cfg_a, &p.parts_a);
     gemm_parts_plan(prec, p.rg, W, 4 * pack_geom(1, M, 4, 4, prec).Gp / KB, &p.cfg_b, &p.parts_b);
-    // ranges are of use to the kernels for few projections, and to FP32
+    // ranges are of use to a synthesis that reads its input once, and to FP32
     if (r > 16 && prec != PJ_F32) p.parts_a = p.parts_b = 1, p.cfg_a = p.cfg_b = -1;
     p.dahat = off; off += align256((size_t)p.parts_a * M * p.rg * p.T);
     p.dbhat = off; off += align256((size_t)p.parts_b * p.rg * W * p.T);
@@ -903,17 +903,17 @@ int run_bwd(pj_basis b, int r, char transA, char transB, int M, int W, int K, co
         return u;
     };
     // P x Q product over Kc into R (row stride Q), as `parts` partials for a
-    // synthesis that adds them (`few`); returns their number in `parts`
+    // synthesis that adds them (`once`); returns their number in `parts`
     auto gemm = [&](const void* X, int64_t P, const void* Y, int64_t Q, int64_t Kc, void* R, int cfg, int& parts,
-                    bool few) {
-        if (!few && prec != PJ_F32) cfg = -1, parts = 1;
+                    bool once) {
+        if (!once && prec != PJ_F32) cfg = -1, parts = 1;
         GemmArgs g;
         g.X = X; g.gx = pack_geom(P, Kc, 4, 4, prec);
         g.Y = Y; g.gy = pack_geom(Q, Kc, 4, 4, prec);
         g.nkb = 4 * g.gx.Gp / layout_of(prec).KB;
         g.P = P; g.Q = Q; g.R = R; g.ldr = Q; g.beta = 0.0f;
-        g.nsplit = parts; g.part = parts > 1 ? R : nullptr; g.part_only = few;
-        if (!few) parts = 1;
+        g.nsplit = parts; g.part = parts > 1 ? R : nullptr; g.part_only = once;
+        if (!once) parts = 1;
         return launch_gemm(prec, g, cfg, st);
     };
     // the unprojected operands are only re-laid out (natural contraction
@@ -947,7 +947,7 @@ int run_bwd(pj_basis b, int r, char transA, char transB, int M, int W, int K, co
         // 2. dA_hat = dR B_hat: contraction over the W columns of R
         int parts = pl.parts_a;
         const int ot = is_t(transA) ? 1 : 0;
-        if (gemm(p1, M, p2, pl.rg, W, w + pl.dahat, pl.cfg_a, parts, expand_few(f64, b->L, r, 0, ot)) != 0)
+        if (gemm(p1, M, p2, pl.rg, W, w + pl.dahat, pl.cfg_a, parts, expand_once(f64, b->L, r, 0, ot)) != 0)
             return PJ_ERR_HIP;
         // 3. dA = dA_hat spread back over each group with C
         ExpandArgs e;
@@ -962,7 +962,7 @@ int run_bwd(pj_basis b, int r, char transA, char transB, int M, int W, int K, co
         // 4. dB_hat = A_hat^T dR: contraction over the M rows of R
         int parts = pl.parts_b;
         const int ot = is_n(transB) ? 1 : 0;
-        if (gemm(p3, pl.rg, p4, W, M, w + pl.dbhat, pl.cfg_b, parts, expand_few(f64, b->L, r, 1, ot)) != 0)
+        if (gemm(p3, pl.rg, p4, W, M, w + pl.dbhat, pl.cfg_b, parts, expand_once(f64, b->L, r, 1, ot)) != 0)
             return PJ_ERR_HIP;
         // 5. dB = dB_hat spread back over each group with D
         ExpandArgs e;

@@ -177,9 +177,8 @@ struct ExpandArgs {
     int nparts = 1; int64_t part = 0;              // in = sum of nparts arrays `part` elements apart, last first
 };
 int launch_expand(int is_double, const ExpandArgs& a, hipStream_t s);
-// Whether a synthesis runs in the kernels for few projections, which read each
-// projected value (and so each partial) once.
-bool expand_few(int is_double, int L, int r, int in_trans, int out_trans);
+// Whether a synthesis reads each projected value (and so each partial) once.
+bool expand_once(int is_double, int L, int r, int in_trans, int out_trans);
 
 // One problem of a grouped launch, as stored in device memory.
 struct GroupedProblem {

@@ -222,10 +222,16 @@ __global__ __launch_bounds__(256) void expand_cols_kernel(const float* __restric
     }
 }
 
-// The kernels above where they apply: 1 launched, 0 not applicable, -1 failed.
+// Whether the kernels above apply (FP32).
+bool expand_few(int L, int r, int in_trans, int out_trans)
+{
+    return r <= 16 && L <= 256 && in_trans == out_trans && (out_trans || L % 4 == 0);
+}
+
+// Runs them where they do: 1 launched, 0 not applicable, -1 failed.
 int launch_few(const ExpandArgs& a, hipStream_t s)
 {
-    if (!expand_few(0, a.L, a.r, a.in_trans, a.out_trans)) return 0;
+    if (!expand_few(a.L, a.r, a.in_trans, a.out_trans)) return 0;
     const int64_t G = cdiv(a.K, a.L);
 #define PJ_EXF(KERN_, RC_, GX_, GY_, ...)                                                                        \
     hipLaunchKernelGGL(KERN_<RC_>, dim3((unsigned)(GX_), (unsigned)(GY_)), dim3(256), 0, s, (const float*)a.in, a.ldi, \
@@ -278,9 +284,11 @@ int launch_t(const ExpandArgs& a, hipStream_t s)
 
 }  // namespace
 
-bool expand_few(int is_double, int L, int r, int in_trans, int out_trans)
+// Whether the synthesis reads every partial of its input once: the kernels for few
+// projections, and the general one where a group is a single pass.
+bool expand_once(int is_double, int L, int r, int in_trans, int out_trans)
 {
-    return !is_double && r <= 16 && L <= 256 && in_trans == out_trans && (out_trans || L % 4 == 0);
+    return !is_double && (L <= kExpandChunk || expand_few(L, r, in_trans, out_trans));
 }
 
 int launch_expand(int is_double, const ExpandArgs& a, hipStream_t s)

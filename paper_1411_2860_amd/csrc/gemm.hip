@@ -1557,7 +1557,8 @@ int gemm_split_count(int prec, int64_t P, int64_t Q, int64_t nkb, int cfg)
 // most 8 ranges (each is a pass over a P x Q array for the consumer).  4096 x 512
 // over 4096, BF16, as the 64 x 64 direct tiles of gemm_default_config: 44.5 us,
 // as four ranges of 64 tiles: 28.5 us, their sum inside the synthesis.  That is
-// for the synthesis that reads every partial once (expand_few); where it reads
+// for the synthesis that reads every partial once (expand_once; 6016 x 1792 over 2816, FP16,
+// both transposed, L = 16, r = 11: 243 us, without ranges 291); where it reads
 // them for every 16 outputs, the 16-bit formats do better without ranges (whole
 // backward, 256 x 4096 over 4096, L = 64, r = 32: 111 us, 129 us with them; 512 x 2048 over 2048,
 // L = r = 32: 65 and 74 us) and FP32 with ranges added up by a kernel of its own

@@ -100,3 +100,11 @@ def test_batch_configuration(prec, default, shapes, small):
     assert auto == chosen > 0
     if default == 16 and shapes[0][0] > 8:                # FP32's two have tiles of one size
         assert pg.gemm_batched_workspace_bytes(descs, 16, 4, prec, default if small else 0) != auto
+
+
+@pytest.mark.parametrize("f64,L,r,in_trans,out_trans,once", [
+    (0, 16, 11, 0, 1, 1), (0, 10, 4, 0, 0, 1), (0, 17, 4, 0, 0, 0), (0, 20, 11, 0, 1, 0), (0, 20, 11, 0, 0, 1),
+    (0, 64, 16, 1, 1, 1), (0, 64, 17, 1, 1, 0), (0, 64, 16, 1, 0, 0), (1, 8, 2, 0, 0, 0)])
+def test_synthesis_reads_once(rule, f64, L, r, in_trans, out_trans, once):
+    f = rule("_ZN2pj11expand_onceEiiiii", ctypes.c_bool, *[ctypes.c_int] * 5)
+    assert f(f64, L, r, in_trans, out_trans) == bool(once)
